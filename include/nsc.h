@@ -253,8 +253,9 @@ int nsc_get_grid(nsc_ctx *ctx, double *r_host, int n);
  * (nsc_remap_state, and nsc_load_state at another resolution), [4]
  * right sides, [5] Poisson right side (and temperature wall
  * rows), [6] pressure/temperature sweeps, [7] velocity sweeps, [8] influence
- * coefficients, [9] finalisation, [10] factorisation, [11] velocity right
- * sides (f - grad p); entries [12..23] the launch counts of the same
+ * coefficients, [9] finalisation (up to 128 radial points: the whole
+ * implicit stage, which is one kernel there; [4]-[8] and [11] stay zero),
+ * [10] factorisation, [11] velocity right sides (f - grad p); entries [12..23] the launch counts of the same
  * kernels.  Counters are reset by the call.  Timing is enabled by
  * nsc_set_profiling(ctx, 1): each kernel is then bracketed by HIP events on
  * the context stream and the host waits for the second event. */

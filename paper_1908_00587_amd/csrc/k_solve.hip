@@ -15,26 +15,10 @@
 
 #include <type_traits>
 
-#include "nsc_internal.h"
+#include "solve_common.h"
 
 namespace nsc {
 namespace {
-
-__device__ __forceinline__ int edge_off(int t) { return t * 4 - (t * (t - 1)) / 2; }
-
-struct Cd {
-  double x, y;
-};
-__device__ __forceinline__ Cd operator+(Cd a, Cd b) { return {a.x + b.x, a.y + b.y}; }
-__device__ __forceinline__ Cd operator-(Cd a, Cd b) { return {a.x - b.x, a.y - b.y}; }
-__device__ __forceinline__ Cd operator*(double s, Cd a) { return {s * a.x, s * a.y}; }
-__device__ __forceinline__ Cd ci(Cd a) { return {-a.y, a.x}; }  // i * a
-__device__ __forceinline__ Cd ld(const double2 *p) {
-  double2 v = *p;
-  return {v.x, v.y};
-}
-__device__ __forceinline__ void st(double2 *p, Cd v) { *p = make_double2(v.x, v.y); }
-__device__ __forceinline__ Cd fmac(double w, Cd v, Cd acc) { return {fma(w, v.x, acc.x), fma(w, v.y, acc.y)}; }
 
 // Matrix entry A[i][c] of an operator for c in the window of row i.  pipe:
 // row 0 is an inner row (the axis is no boundary) and the derivative rows
@@ -285,19 +269,14 @@ __device__ __forceinline__ void lu_solve(const Factors &F, int op, int nrt, RHS 
   }
 }
 
-struct Rd {
-  double v;
-};
-__device__ __forceinline__ Rd operator-(Rd a, Rd b) { return {a.v - b.v}; }
-__device__ __forceinline__ Rd operator*(double s, Rd a) { return {s * a.v}; }
-
-__device__ __forceinline__ double d1_row(const Grid &g, int j, const double *x, size_t stride,
-                                        int off = 0) {
+// The two responses (Neumann data at r_i, at r_o) of one operator: solved
+// together, so that a lane reads each factor row once for both.
+__device__ __forceinline__ Cd d1_row(const Grid &g, int j, const Cd *x, size_t stride, int off = 0) {
   const int s = g.s[j];
   const double *w = g.d1 + off + j * kStencil;
-  double acc = 0.0;
+  Cd acc = {0.0, 0.0};
 #pragma unroll
-  for (int t = 0; t < kStencil; ++t) acc = fma(w[t], x[(size_t)(s + t) * stride], acc);
+  for (int t = 0; t < kStencil; ++t) acc = fmac(w[t], x[(size_t)(s + t) * stride], acc);
   return acc;
 }
 
@@ -307,68 +286,68 @@ __device__ __forceinline__ double d1_row(const Grid &g, int j, const double *x, 
 // (X+, X-, h for each p_j) in parallel, then the 2x2 influence matrices.
 __global__ void __launch_bounds__(64) k_influence_p(Dims d, Factors fp, Influence I) {
   const int op = blockIdx.x * blockDim.x + threadIdx.x;
-  const int jj = blockIdx.y;  // 0: data at r_i, 1: at r_o
   if (op >= I.nops) return;
   const int n = d.nr;
   const int kp1 = d.kmax + 1;
   const int m = op / kp1;
   const int ka = op - m * kp1;
   const size_t ns = I.nops;
-  double *Pj = I.resp + (size_t)jj * n * ns + op;
+  Cd *P = reinterpret_cast<Cd *>(I.resp) + op;
   if (m == 0 && ka == 0) {
-    for (int j = 0; j < n; ++j) Pj[(size_t)j * ns] = 0.0;
+    for (int j = 0; j < n; ++j) P[(size_t)j * ns] = Cd{0.0, 0.0};
     return;
   }
-  const int wall = jj == 0 ? 0 : n - 1;
-  lu_solve<Rd>(fp, op, n, [&](int j) { return Rd{j == wall ? 1.0 : 0.0}; },
-               [&](int j) -> Rd & { return *reinterpret_cast<Rd *>(&Pj[(size_t)j * ns]); });
+  lu_solve<Cd>(fp, op, n, [&](int j) { return Cd{j == 0 ? 1.0 : 0.0, j == n - 1 ? 1.0 : 0.0}; },
+               [&](int j) -> Cd & { return P[(size_t)j * ns]; });
 }
+
+constexpr int kInfLanes = 32;  // operators per workgroup with the columns in LDS
 
 template <bool USE_LDS>
 __global__ void __launch_bounds__(64) k_influence_x(Dims d, Grid g, Factors fv, Influence I) {
-  extern __shared__ double inf_lds[];  // USE_LDS: [2][N_r][64] pressure and solution columns
-  const int op = blockIdx.x * blockDim.x + threadIdx.x;
-  const int jj = blockIdx.y;    // which pressure response
-  const int kind = blockIdx.z;  // 0: X+, 1: X-, 2: h
+  extern __shared__ Cd inf_lds[];  // USE_LDS: [2][N_r][lanes] pressure and solution columns
+  const int lanes = blockDim.x;
+  const int op = blockIdx.x * lanes + threadIdx.x;
+  const int kind = blockIdx.y;  // 0: X+, 1: X-, 2: h
   if (op >= I.nops) return;
   const int n = d.nr;
   const int kp1 = d.kmax + 1;
   const int m = op / kp1;
   const int ka = op - m * kp1;
   const size_t ns = I.nops;
-  double *out = I.resp + (size_t)(2 + 2 * kind + jj) * n * ns + op;
+  Cd *resp = reinterpret_cast<Cd *>(I.resp) + op;
+  Cd *out = resp + (size_t)(1 + kind) * n * ns;
   if (m == 0 && ka == 0) {
-    for (int j = 0; j < n; ++j) out[(size_t)j * ns] = 0.0;
+    for (int j = 0; j < n; ++j) out[(size_t)j * ns] = Cd{0.0, 0.0};
     return;
   }
   const double mm = (double)m;
-  const double *Pj = I.resp + (size_t)jj * n * ns + op;
   const int q = kind == 0 ? m + 1 : (kind == 1 ? (m >= 1 ? m - 1 : 1 - m) : m);
   // X+ = H_{m+1}^-1 (-(D1 p - m p / r)), X- = H_{|m-1|}^-1 (-(D1 p + m p / r)),
   // h = H_m^-1 p so that X_z = -i kappa h
-  auto rhs = [&](int j, const double *p, size_t stride) {
-    if ((j == 0 && !d.pipe) || j == n - 1) return Rd{0.0};
-    const double pj = p[(size_t)j * stride];
-    if (kind == 2) return Rd{pj};
-    const double dp = d1_row(g, j, p, stride, odd_off(g, m));  // p of order m
-    const double mp = mm * g.rinv[j] * pj;
-    return Rd{kind == 0 ? -(dp - mp) : -(dp + mp)};
+  auto rhs = [&](int j, const Cd *p, size_t stride) {
+    if ((j == 0 && !d.pipe) || j == n - 1) return Cd{0.0, 0.0};
+    const Cd pj = p[(size_t)j * stride];
+    if (kind == 2) return pj;
+    const Cd dp = d1_row(g, j, p, stride, odd_off(g, m));  // p of order m
+    const Cd mp = (mm * g.rinv[j]) * pj;
+    return kind == 0 ? Cd{0.0, 0.0} - (dp - mp) : Cd{0.0, 0.0} - (dp + mp);
   };
   if constexpr (USE_LDS) {
     // each lane owns one pressure column and one solution column in LDS (no
     // sharing, so no barrier): the back substitution and the stencil reads
     // stay on chip
-    double *pl = inf_lds + threadIdx.x;
-    double *xl = inf_lds + (size_t)n * 64 + threadIdx.x;
+    Cd *pl = inf_lds + threadIdx.x;
+    Cd *xl = inf_lds + (size_t)n * lanes + threadIdx.x;
 #pragma unroll 8
-    for (int j = 0; j < n; ++j) pl[j * 64] = Pj[(size_t)j * ns];
-    lu_solve<Rd>(fv, q * kp1 + ka, n, [&](int j) { return rhs(j, pl, 64); },
-                 [&](int j) -> Rd & { return *reinterpret_cast<Rd *>(&xl[j * 64]); });
+    for (int j = 0; j < n; ++j) pl[j * lanes] = resp[(size_t)j * ns];
+    lu_solve<Cd>(fv, q * kp1 + ka, n, [&](int j) { return rhs(j, pl, lanes); },
+                 [&](int j) -> Cd & { return xl[j * lanes]; });
 #pragma unroll 8
-    for (int j = 0; j < n; ++j) out[(size_t)j * ns] = xl[j * 64];
+    for (int j = 0; j < n; ++j) out[(size_t)j * ns] = xl[j * lanes];
   } else {
-    lu_solve<Rd>(fv, q * kp1 + ka, n, [&](int j) { return rhs(j, Pj, ns); },
-                 [&](int j) -> Rd & { return *reinterpret_cast<Rd *>(&out[(size_t)j * ns]); });
+    lu_solve<Cd>(fv, q * kp1 + ka, n, [&](int j) { return rhs(j, resp, ns); },
+                 [&](int j) -> Cd & { return out[(size_t)j * ns]; });
   }
 }
 
@@ -388,15 +367,15 @@ __global__ void __launch_bounds__(64) k_influence_a(Dims d, Grid g, Influence I)
   // A[w][jj] = wall divergence of response jj (walls carry zero velocity)
   double A[2][2];
   const int off = odd_off(g, m + 1);  // X+- of orders m +- 1
-  for (int jj = 0; jj < 2; ++jj) {
-    const double *Xp = I.resp + (size_t)(2 + jj) * n * ns + op;
-    const double *Xm = I.resp + (size_t)(4 + jj) * n * ns + op;
-    for (int w = 0; w < 2; ++w) {
-      const int j = w == 0 ? 0 : n - 1;
-      const double ri = g.rinv[j];
-      A[w][jj] = 0.5 * ((d1_row(g, j, Xp, ns, off) + (1.0 + mm) * ri * Xp[(size_t)j * ns]) +
-                        (d1_row(g, j, Xm, ns, off) + (1.0 - mm) * ri * Xm[(size_t)j * ns]));
-    }
+  const Cd *Xp = reinterpret_cast<const Cd *>(I.resp) + (size_t)n * ns + op;
+  const Cd *Xm = Xp + (size_t)n * ns;
+  for (int w = 0; w < 2; ++w) {
+    const int j = w == 0 ? 0 : n - 1;
+    const double ri = g.rinv[j];
+    const Cd v = 0.5 * ((d1_row(g, j, Xp, ns, off) + ((1.0 + mm) * ri) * Xp[(size_t)j * ns]) +
+                        (d1_row(g, j, Xm, ns, off) + ((1.0 - mm) * ri) * Xm[(size_t)j * ns]));
+    A[w][0] = v.x;
+    A[w][1] = v.y;
   }
   if (d.pipe) {
     // one wall: the first condition becomes lambda_1 = 0 (k_influence gives
@@ -1042,12 +1021,16 @@ __device__ __forceinline__ Vals final_value(const Dims &d, const Influence &I,
     const Cd l1 = ld(lam + 2 * (size_t)md), l2 = ld(lam + 2 * (size_t)md + 1);
     const size_t ns = I.nops;
     const int op = m * kp1 + ka;
-    auto Rv = [&](int s) { return I.resp[((size_t)s * n + j) * ns + op]; };
-    if (WITH_P) p = p + Rv(0) * l1 + Rv(1) * l2;
-    xp = xp + Rv(2) * l1 + Rv(3) * l2;
-    xm = xm + Rv(4) * l1 + Rv(5) * l2;
+    // the pair of responses of kind s (p, X+, X-, h) times lambda
+    auto hom = [&](int s) {
+      const double2 r = I.resp[((size_t)s * n + j) * ns + op];
+      return r.x * l1 + r.y * l2;
+    };
+    if (WITH_P) p = p + hom(0);
+    xp = xp + hom(1);
+    xm = xm + hom(2);
     // X_z,j = -i kappa h_j
-    const Cd hz = Rv(6) * l1 + Rv(7) * l2;
+    const Cd hz = hom(3);
     xz = xz - kap * ci(hz);
   }
   v.ur = 0.5 * (xp + xm);
@@ -1371,8 +1354,9 @@ k_adj_lambda(Dims d, Influence I, const double2 *__restrict__ sx, double2 *__res
       const Cd xm = ld(sx + ((size_t)n + j) * P + md);
       const Cd xz = kap * ci(ld(sx + ((size_t)2 * n + j) * P + md));  // i kappa Xbar_z
       auto Rv = [&](int s) { return I.resp[((size_t)s * n + j) * ns + op]; };
-      l1 = l1 + (Rv(2) * xp + Rv(4) * xm + Rv(6) * xz);
-      l2 = l2 + (Rv(3) * xp + Rv(5) * xm + Rv(7) * xz);
+      const double2 r1 = Rv(1), r2 = Rv(2), r3 = Rv(3);
+      l1 = l1 + (r1.x * xp + r2.x * xm + r3.x * xz);
+      l2 = l2 + (r1.y * xp + r2.y * xm + r3.y * xz);
     }
   }
   if (q > 0) {
@@ -1910,22 +1894,24 @@ hipError_t launch_factor2(const nsc_ctx *c, Factors *f0, Factors *f1, int kind, 
 }
 
 hipError_t launch_influence_pressure(const nsc_ctx *c) {
-  hipLaunchKernelGGL(k_influence_p, dim3((c->inf.nops + 63) / 64, 2), dim3(64), 0, c->stream, c->d,
+  hipLaunchKernelGGL(k_influence_p, dim3((c->inf.nops + 63) / 64), dim3(64), 0, c->stream, c->d,
                      c->fp, c->inf);
   return hipGetLastError();
 }
 
 hipError_t launch_influence_setup(const nsc_ctx *c) {
-  const dim3 gx((c->inf.nops + 63) / 64, 2, 3);
+  const dim3 gx((c->inf.nops + kInfLanes - 1) / kInfLanes, 3);
   // LDS columns only while every workgroup is resident at once: the solves
   // are latency chains, and at larger sizes the LDS would cap the waves in
   // flight below what the global-memory variant keeps
-  const size_t shm = (size_t)2 * c->d.nr * 64 * sizeof(double);
+  const size_t shm = (size_t)2 * c->d.nr * kInfLanes * sizeof(Cd);
   const size_t resident = shm <= (size_t)c->lds_max ? (size_t)c->cu_count * (c->lds_cu / shm) : 0;
-  if ((size_t)gx.x * gx.y * gx.z <= resident)
-    hipLaunchKernelGGL(k_influence_x<true>, gx, dim3(64), shm, c->stream, c->d, c->g, c->fv, c->inf);
+  if ((size_t)gx.x * gx.y <= resident)
+    hipLaunchKernelGGL(k_influence_x<true>, gx, dim3(kInfLanes), shm, c->stream, c->d, c->g, c->fv,
+                       c->inf);
   else
-    hipLaunchKernelGGL(k_influence_x<false>, gx, dim3(64), 0, c->stream, c->d, c->g, c->fv, c->inf);
+    hipLaunchKernelGGL(k_influence_x<false>, dim3((c->inf.nops + 63) / 64, 3), dim3(64), 0,
+                       c->stream, c->d, c->g, c->fv, c->inf);
   hipLaunchKernelGGL(k_influence_a, dim3((c->inf.nops + 63) / 64), dim3(64), 0, c->stream, c->d,
                      c->g, c->inf);
   return hipGetLastError();

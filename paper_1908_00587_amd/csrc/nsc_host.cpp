@@ -224,6 +224,11 @@ int nonlinear_impl(nsc_ctx *c, const double *u, double *nh, double *cfl_out,
 int solve_impl(nsc_ctx *c, const double *un, const double *nn, const double *nq, double *out,
                double *pout, double dt, double cc, int walls) {
   TRY(ensure_factors(c, dt, cc));
+  if (c->fused) {
+    StageTimer t(c, 9);
+    HIPCHK(launch_stage(c, un, nn, nq, out, pout, dt, cc, walls));
+    return NSC_OK;
+  }
   {
     StageTimer t(c, 4);
     HIPCHK(launch_rhs(c, un, nn, nq, dt, cc));
@@ -594,16 +599,20 @@ static int init_impl(nsc_ctx *c, double eta, double Re_i, double Re_o, double Ra
 
   // factors
   const int kp1 = d.kmax + 1;
-  const bool packed = sweeps_unrolled(d, (d.mt + 1) * kp1);
+  const bool columns = sweeps_unrolled(d, (d.mt + 1) * kp1);
+  c->fused = stage_fused(c) ? 1 : 0;
+  const bool packed = c->fused || columns;
   TRY(alloc_factors(&c->fv, d.mt + 1, kp1, n, packed));
   TRY(alloc_factors(&c->fp, d.mt, kp1, n, packed));
   if (d.heated) TRY(alloc_factors(&c->ft, d.mt, kp1, n, packed));
   c->inf.nops = d.mt * kp1;
   TRY(dmalloc((void **)&c->inf.resp, (size_t)8 * n * c->inf.nops * sizeof(double)));
   TRY(dmalloc((void **)&c->inf.ainv, (size_t)4 * c->inf.nops * sizeof(double)));
-  TRY(alloc_columns(&c->fv, n));
-  TRY(alloc_columns(&c->fp, n));
-  if (d.heated) TRY(alloc_columns(&c->ft, n));
+  if (columns) {
+    TRY(alloc_columns(&c->fv, n));
+    TRY(alloc_columns(&c->fp, n));
+    if (d.heated) TRY(alloc_columns(&c->ft, n));
+  }
 
   // Delta t-independent pressure factors (slot (0,0): the mean pressure head)
   HIPCHK(launch_factor(c, &c->fp, OP_POISSON, 0.0, 0.0));

@@ -85,10 +85,11 @@ inline bool sweeps_unrolled(const Dims &d, int nops_max) {
 }
 
 // Homogeneous (influence) responses per (m, |k|), op = m*(K+1)+|k|:
-// resp: [8][N_r][nops] = p1, p2, X+1, X+2, X-1, X-2, h1, h2 (X_z,j = -i kappa h_j)
+// resp: [4][N_r][nops] pairs (response to data at r_i, at r_o) of p, X+, X-,
+// h (X_z,j = -i kappa h_j): the two are always used together, one 16-byte load
 // ainv: [4][nops] the inverse 2x2 influence matrix.
 struct Influence {
-  double *resp = nullptr;
+  double2 *resp = nullptr;
   double *ainv = nullptr;
   int nops = 0;
 };
@@ -108,6 +109,7 @@ struct nsc_ctx {
   int device = 0;
   int lds_max = 64 * 1024;  // dynamic LDS bytes per workgroup (device limit)
   int cu_count = 256;       // compute units
+  int fused = 0;            // the implicit stage runs as one kernel
   int rows_first = 0;       // stencil kernels walk rows first (long radial rows)
   int lds_cu = 160 * 1024;  // LDS bytes per compute unit
   // host copies
@@ -205,6 +207,12 @@ hipError_t launch_fill_zero(const nsc_ctx *c, double *p, size_t n);
 hipError_t launch_add(const nsc_ctx *c, double *y, const double *x, size_t n);
 hipError_t launch_solve_sweeps(const nsc_ctx *c, int stage, const double *nn, const double *nq,
                                double cc, int walls, int want_p);
+// the whole implicit stage in one kernel, for grids of up to kStageRows
+// radial points (stage_fused); u may be out
+constexpr int kStageRows = 128;
+bool stage_fused(const nsc_ctx *c);
+hipError_t launch_stage(const nsc_ctx *c, const double *u, const double *nn, const double *nq,
+                        double *out, double *pout, double dt, double cc, int walls);
 hipError_t launch_influence(const nsc_ctx *c);
 hipError_t launch_finalize(const nsc_ctx *c, double *out, double *p_out);
 hipError_t launch_energy(const nsc_ctx *c, const double *u, double *e_dev);
