@@ -526,19 +526,18 @@ __device__ __forceinline__ void fft_wave_ct(C2<T> *buf, int nlines, const TwT<T>
   }
 }
 
-// Radix orders of the fixed lengths n = 3 * 2^a: ORD_PLAN the planner's
-// (powers of two, then radix 3), ORD_3FIRST radix 3 first, then the
-// planner's powers of two.  In a 3-first transform the first stage's
+// Radix orders of the fixed lengths: the planner's with one radix 3 moved to
+// the front (ORD_3FIRST) or to the end (ORD_3LAST; the planner's own order
+// unless the length has a factor 5).  In a 3-first transform the first stage's
 // butterflies read elements j, j + n/3, j + 2n/3, so the zero third of a
 // Hermitian-extended line (positions M..2M of a 3M-point line) falls on the
 // middle leg of every butterfly.
-enum { ORD_PLAN = 0, ORD_3FIRST = 1 };
+enum { ORD_3LAST = 0, ORD_3FIRST = 1 };
 
 constexpr CtRadices ct_order(int n, int ord) {
   const CtRadices p = ct_radices(n);
-  if (ord == ORD_PLAN) return p;
   CtRadices q{0, {}};
-  q.r[q.nst++] = 3;
+  if (ord == ORD_3FIRST) q.r[q.nst++] = 3;
   bool dropped = false;
   for (int i = 0; i < p.nst; ++i) {
     if (p.r[i] == 3 && !dropped) {
@@ -547,6 +546,7 @@ constexpr CtRadices ct_order(int n, int ord) {
     }
     q.r[q.nst++] = p.r[i];
   }
+  if (ord == ORD_3LAST) q.r[q.nst++] = 3;
   return q;
 }
 
