@@ -92,8 +92,8 @@ def kernel_bytes(name, w, prec):
 STAGE_KERNELS = {"theta": ("nsc::k_theta<float,", "nsc::k_theta_fx<float,"),
                  "zinv": ("nsc::k_zinv<float,",), "zfwd": ("nsc::k_zfwd<float,",),
                  "rhs": ("nsc::k_rhs<",), "div": ("nsc::k_div2<",),
-                 "sweep_pt": ("nsc::k_sweep<true, 0,", "nsc::k_sweep<false, 0,"),
-                 "sweep_vel": ("nsc::k_sweep<true, 1,", "nsc::k_sweep<false, 1,"),
+                 "sweep_pt": ("nsc::k_sweep<true, 0,", "nsc::k_sweep<false, 0,", "nsc::k_sweep<0>"),
+                 "sweep_vel": ("nsc::k_sweep<true, 1,", "nsc::k_sweep<false, 1,", "nsc::k_sweep<1>"),
                  "vel_rhs": ("nsc::k_vel_rhs<",), "finalize": ("nsc::k_finalize<false>",),
                  "influence": ("nsc::k_influence<",), "stage": ("nsc::k_stage<",)}
 

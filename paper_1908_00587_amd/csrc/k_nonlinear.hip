@@ -7,8 +7,12 @@ namespace nsc {
 namespace {
 
 // ubar += D(u)^T dbar (transposes of the spectral curl/gradient) + buoyancy.
-__global__ void k_derived_adj(Dims d, Grid g, const double2 *__restrict__ db,
-                              const double2 *__restrict__ nb, double2 *__restrict__ ub) {
+// (WRITE: ubar = instead of +=; tables: the transposed rows of D1)
+template <bool WRITE>
+__global__ void __launch_bounds__(256)
+k_derived_adj(Dims d, Grid g, const int *__restrict__ trow, const int *__restrict__ tcnt,
+              const double *__restrict__ twd, const double2 *__restrict__ db,
+              const double2 *__restrict__ nb, double2 *__restrict__ ub) {
   const int md = blockIdx.x * blockDim.x + threadIdx.x;
   const int j = blockIdx.y;
   if (md >= d.nmodes) return;
@@ -20,27 +24,27 @@ __global__ void k_derived_adj(Dims d, Grid g, const double2 *__restrict__ db,
   const double ri = g.rinv[j];
   const double mr = (double)m * ri;
   auto D = [&](int f) { return db[((size_t)f * n + j) * P + md]; };
-  // (D1^T v)_j over the rows whose window holds j
+  // (D1^T v)_j over the rows whose window holds j (uniform per workgroup)
+  const int cnt = tcnt[j];
   auto D1T = [&](int f) {
     double2 acc = make_double2(0.0, 0.0);
-    const int lo = j - 8 < 0 ? 0 : j - 8;
-    const int hi = j + 8 > n - 1 ? n - 1 : j + 8;
-    for (int i = lo; i <= hi; ++i) {
-      const int t = j - g.s[i];
-      if (t >= 0 && t < kStencil) {
-        const double w = g.d1[i * kStencil + t];
-        const double2 v = db[((size_t)f * n + i) * P + md];
-        acc.x = fma(w, v.x, acc.x);
-        acc.y = fma(w, v.y, acc.y);
-      }
+    for (int e = 0; e < cnt; ++e) {
+      const double w = twd[j * kTrans + e];
+      const double2 v = db[((size_t)f * n + trow[j * kTrans + e]) * P + md];
+      acc.x = fma(w, v.x, acc.x);
+      acc.y = fma(w, v.y, acc.y);
     }
     return acc;
   };
   auto mul_i = [](double s, double2 v) { return make_double2(-s * v.y, s * v.x); };  // i s v
   auto add = [&](int f, double2 v) {
     double2 *p = ub + ((size_t)f * n + j) * P + md;
-    p->x += v.x;
-    p->y += v.y;
+    if (WRITE) {
+      *p = v;
+    } else {
+      p->x += v.x;
+      p->y += v.y;
+    }
   };
   const double2 d0 = D(0), d1 = D(1), d2 = D(2), d3 = D(3), d4 = D(4), d5 = D(5);
   const double2 a4 = mul_i(-kap, d4), a5 = mul_i(mr, d5);
@@ -147,7 +151,8 @@ hipError_t theta_adj_any(const nsc_ctx *c) {
 }
 
 template <typename T>
-hipError_t nonlinear_vjp_impl(const nsc_ctx *c, const double *u, const double *nbar, double *ubar) {
+hipError_t nonlinear_vjp_impl(const nsc_ctx *c, const double *u, const double *nbar, double *ubar,
+                              int overwrite) {
   const LenOps o = z_ops<T>(c);
   // forward fields and output adjoints on the (r, theta-spectral, z-physical)
   // grid, pointwise adjoint, input adjoints back
@@ -156,8 +161,9 @@ hipError_t nonlinear_vjp_impl(const nsc_ctx *c, const double *u, const double *n
   if (e == hipSuccess) e = theta_adj_any<T>(c);
   if (e == hipSuccess) e = o.zfwd_adj(c);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_derived_adj, dim3((c->d.nmodes + 255) / 256, c->d.nr), dim3(256), 0, c->stream,
-                     c->d, c->g, reinterpret_cast<const double2 *>(c->s_adj),
+  auto kern = overwrite ? k_derived_adj<true> : k_derived_adj<false>;
+  hipLaunchKernelGGL(kern, dim3((c->d.nmodes + 255) / 256, c->d.nr), dim3(256), 0, c->stream,
+                     c->d, c->g, c->t_row, c->t_cnt, c->t_wd, reinterpret_cast<const double2 *>(c->s_adj),
                      reinterpret_cast<const double2 *>(nbar), reinterpret_cast<double2 *>(ubar));
   return hipGetLastError();
 }
@@ -189,9 +195,9 @@ hipError_t launch_zfwd(const nsc_ctx *c, int prec, const double *u, double *n_ha
 }
 
 hipError_t launch_nonlinear_vjp(const nsc_ctx *c, int prec, const double *u, const double *nbar,
-                                double *ubar) {
-  if (prec == NSC_MIXED) return nonlinear_vjp_impl<float>(c, u, nbar, ubar);
-  return nonlinear_vjp_impl<double>(c, u, nbar, ubar);
+                                double *ubar, int overwrite) {
+  if (prec == NSC_MIXED) return nonlinear_vjp_impl<float>(c, u, nbar, ubar, overwrite);
+  return nonlinear_vjp_impl<double>(c, u, nbar, ubar, overwrite);
 }
 
 }  // namespace nsc

@@ -178,12 +178,6 @@ k_factor(Dims d, Grid g, Factors F0, Factors F1, int kind, double alpha, double 
         at(F.pk, k, 0)[t] = lo[t];
         at(F.pk, k, 1)[t] = up[t];
       }
-      // L(k, k - t) in column k - t, U(k, k + t) in column k + t
-      if (F.pc)
-        for (int t = 1; t <= 4; ++t) {
-          if (k - t >= 0) at(F.pc, k - t, 0)[t - 1] = lo[4 - t];
-          if (k + t < n) at(F.pc, k + t, 1)[t - 1] = up[t - 1];
-        }
     }
     if (k <= 3)
       for (int c = k + 5; c <= 8 && c < n; ++c)
@@ -204,17 +198,13 @@ k_factor(Dims d, Grid g, Factors F0, Factors F1, int kind, double alpha, double 
 // compiler can schedule them ahead of the recurrence; only the one-sided
 // wall rows (U to column 8 in rows 0..3, L from column N-9 in rows N-4..N-1)
 // take the extra edge terms, in peeled loops.
-template <typename V, int NR = 0, typename RHS, typename COL>
-__device__ __forceinline__ void lu_solve(const Factors &F, int op, int nrt, RHS rhs, COL col) {
-  // NR > 0: the row count is a compile-time constant and every loop unrolls
-  // fully (COL may then name registers)
-  const int n = NR > 0 ? NR : nrt;
-  constexpr int kU = NR > 0 ? NR : 4;
+template <typename V, typename RHS, typename COL>
+__device__ __forceinline__ void lu_solve(const Factors &F, int op, int n, RHS rhs, COL col) {
   const size_t nops = F.nops;
   const double *__restrict__ vals = F.vals + op;
   const double *__restrict__ edge = F.edge + op;
   V y1{}, y2{}, y3{}, y4{};
-#pragma unroll kU
+#pragma unroll 4
   for (int j = 0; j < n - 4; ++j) {
     const double *v = vals + (size_t)j * kSlots * nops;
     const double l4 = v[0], l3 = v[nops], l2 = v[2 * nops], l1 = v[3 * nops];
@@ -241,7 +231,7 @@ __device__ __forceinline__ void lu_solve(const Factors &F, int op, int nrt, RHS 
     col(j) = y;
   }
   V x1{}, x2{}, x3{}, x4{};
-#pragma unroll kU
+#pragma unroll 4
   for (int j = n - 1; j >= 4; --j) {
     const double *v = vals + (size_t)j * kSlots * nops;
     const double di = v[4 * nops], u1 = v[5 * nops], u2 = v[6 * nops], u3 = v[7 * nops], u4 = v[8 * nops];
@@ -522,26 +512,9 @@ __global__ void __launch_bounds__(256) k_rhs(Dims d, Grid g, const double2 *__re
 
 // ---------------------------------------------------------------------------
 // Batched sweeps: one lane per (mode, system), the system's right side given
-// column-wise in global memory (rows strided by the mode count).  The
-// intermediate y and the solution x stay in LDS (64 lanes x N_r complex) so
-// the two recurrences issue no global stores and the factor / right-side
-// loads of later rows can be scheduled ahead; the solution is copied out at
-// the end.  Columns longer than the LDS budget keep y in the output array.
+// column-wise in global memory (rows strided by the mode count); y and x stay
+// in the output array.
 // ---------------------------------------------------------------------------
-// Fourth word of a raw buffer resource on CDNA (gfx9 family): 32-bit data
-// format, no swizzle; with stride 0 the record count is a byte count and
-// loads past it return zero.
-constexpr int kBufferWord3 = 0x00020000;
-
-// Raw buffer resource over `bytes` bytes of factor data at base, for the
-// fully unrolled sweeps (NR > 0), whose factor arrays the host keeps below
-// 2^31 bytes; the other variants never read through it and get an empty one.
-template <int NR>
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t sweep_rsrc(const double *base, size_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<double *>(base), 0,
-                                           NR > 0 ? (int)bytes : 0, kBufferWord3);
-}
-
 struct SweepSys {
   Factors F;
   int qmode;   // 0: q = m, 1: q = m + 1, 2: q = |m - 1|
@@ -554,27 +527,11 @@ struct SweepArgs {
 };
 constexpr int kSweepLanes = 64;
 
-// factor rows in flight per sweep: fully unrolled sweeps (issued in that
-// order by scheduling barriers; 16 or 20 rows measure the same), and runtime
-// row counts
-constexpr int kPfUnrolled = 12;
-constexpr int kPfRuntime = 16;
-constexpr int kPc = 4;  // column entries read ahead per sweep (divides the ring depths)
-static_assert(kPfUnrolled % kPc == 0 && kPfRuntime % kPc == 0,
-              "the column ring follows the factor ring");
-
 // FAMILY only names the launch (0: pressure/temperature, 1: velocity), so
 // that profiles tell the two apart; the code is the same.
-// NR > 0: the number of radial points as a compile-time constant, so that
-// the row loops unroll completely and the memory-wait counters can track
-// each prefetched factor row individually (with a rolled loop the waits at
-// the loop head drain every outstanding load).
-template <bool USE_LDS, int FAMILY, int NR>
+template <int FAMILY>
 __global__ void __launch_bounds__(kSweepLanes)
 k_sweep(Dims d, SweepArgs a) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  Cd *col = reinterpret_cast<Cd *>(smem);
-  const int lane = threadIdx.x;
   // logical (mode tile, system) after the XCD remap, system fastest: the
   // two halves of a tile row (m, +-k) use the same operators, and the
   // systems of neighbouring rows share them (q = m - 1, m, m + 1), so these
@@ -582,14 +539,11 @@ k_sweep(Dims d, SweepArgs a) {
   // its L2 instead of HBM
   const int L = xcd_remap(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
   const int sys = L % gridDim.y;
-  const int md = (L / gridDim.y) * kSweepLanes + lane;
+  const int md = (L / gridDim.y) * kSweepLanes + threadIdx.x;
   if (md >= d.nmodes) return;
   const SweepSys &S = a.s[sys];
   const size_t P = d.nmodes;
-  const int n = NR > 0 ? NR : d.nr;
-  constexpr int kUnrollCol = NR > 0 ? NR : 8;   // column copy
-  constexpr int kUnrollRows = NR > 0 ? NR : 1;  // row groups of the sweeps
-  constexpr int kPf = NR > 0 ? kPfUnrolled : kPfRuntime;
+  const int n = d.nr;
   const int kp1 = d.kmax + 1;
   const int m = md / d.mz;
   const int kk = md - m * d.mz;
@@ -601,200 +555,13 @@ k_sweep(Dims d, SweepArgs a) {
   // which holds the mean pressure-head operator
   const Factors F = S.F;
   const int q = S.qmode == 0 ? m : (S.qmode == 1 ? m + 1 : (m >= 1 ? m - 1 : 1 - m));
-  const int op = q * kp1 + ka;
   if (m == 0 && ka == 0 && S.zero00) {
     for (int j = 0; j < n; ++j) x[(size_t)j * P] = make_double2(0.0, 0.0);
     return;
   }
-  if (!USE_LDS) {
-    lu_solve<Cd>(F, op, n, [&](int j) { return ld(b + (size_t)j * P); },
-                 [&](int j) -> Cd & { return *reinterpret_cast<Cd *>(x + (size_t)j * P); });
-    return;
-  }
-  const size_t nops = F.nops;
-  const double *__restrict__ vals = F.vals + op;
-  const double *__restrict__ edge = F.edge + op;
-  auto C = [&](int j) -> Cd & { return col[j * kSweepLanes + lane]; };
-  // Everything a row needs is requested well before the row: the factor
-  // rows and the right side kPf rows ahead (registers), the column entries
-  // kPc ahead (LDS reads), and the edge rows of both ends at the start.  The
-  // right side enters with the factor rows rather than in a bulk copy before
-  // the sweeps.  (The solution leaves in one copy at the end: stored row by
-  // row during the back substitution, its stores fall under the same wait
-  // counter as the prefetched loads and slowed the velocity sweeps.)  One
-  // wavefront per workgroup: registers are plentiful, and the distance of
-  // these requests is what hides the memory latency of the recurrences.
-  const int nm = n - 4;
-  // Fully unrolled sweeps read the factor rows as raw buffer loads: the
-  // lane's operator offset in one 32-bit register, the row and slot offset
-  // in a scalar register, so no 64-bit address is formed per load and the
-  // registers go to rows in flight (the host picks this variant only while
-  // the factor array spans less than 2^31 bytes).
-  const __amdgpu_buffer_rsrc_t frs =
-      sweep_rsrc<NR>(F.vals, (size_t)n * kSlots * nops * sizeof(double));
-  const int voff = op * (int)sizeof(double);
-  auto row = [&](int j, int sl) -> double {
-    if constexpr (NR > 0)
-      return __builtin_bit_cast(
-          double, __builtin_amdgcn_raw_buffer_load_b64(
-                      frs, voff, (int)(((size_t)j * kSlots + sl) * nops * sizeof(double)), 0));
-    else
-      return vals[((size_t)j * kSlots + sl) * nops];
-  };
-  // The four L entries (part 0) or the four off-diagonal U entries (part 1)
-  // of row j into o[0..3].  Unrolled: two 16-byte loads from the row-packed
-  // copy, so that a row costs three memory instructions with its right side
-  // or its diagonal instead of five.
-  const __amdgpu_buffer_rsrc_t prs = sweep_rsrc<NR>(F.pk, (size_t)n * 8 * nops * sizeof(double));
-  const int poff = op * (int)(4 * sizeof(double));
-  auto quad = [&](int j, int part, double *o) {
-    if constexpr (NR > 0) {
-      const int so = (int)(((size_t)j * 2 + part) * nops * 4 * sizeof(double));
-      const double2 a = __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(prs, poff, so, 0));
-      const double2 c = __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(prs, poff + 16, so, 0));
-      o[0] = a.x;
-      o[1] = a.y;
-      o[2] = c.x;
-      o[3] = c.y;
-    } else {
-#pragma unroll
-      for (int t = 0; t < 4; ++t) o[t] = row(j, part ? 5 + t : t);
-    }
-  };
-  // last four rows (forward) and first four rows (backward): band entries
-  // and the extra envelope entries, requested kPf rows before their use so
-  // that they do not hold registers through the bulk of the sweeps
-  double lt[4][4], le[10], ut[4][5], ue[10];
-  auto load_tail = [&] {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) quad(nm + r, 0, lt[r]);
-#pragma unroll
-    for (int e = 0; e < 10; ++e) le[e] = edge[(size_t)(10 + e) * nops];
-  };
-  auto load_head = [&] {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      ut[r][0] = row(r, 4);
-      quad(r, 1, ut[r] + 1);
-    }
-#pragma unroll
-    for (int e = 0; e < 10; ++e) ue[e] = edge[(size_t)e * nops];
-  };
-  // (runtime row counts: at the start of each sweep)
-  const int tail_at = NR > 0 && nm - kPf > 0 ? nm - kPf : 0;          // forward row
-  const int head_at = NR > 0 && 4 + kPf < n - 1 ? 4 + kPf : n - 1;    // backward row
-  if (tail_at == 0) load_tail();
-  // right sides of the last four rows (after the ring's reach)
-  Cd rt[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) rt[r] = ld(b + (size_t)(nm + r) * P);
-  double fa[kPf][4];
-  Cd rb[kPf];
-#pragma unroll
-  for (int r = 0; r < kPf; ++r) {
-    const int jj = r < nm ? r : nm - 1;
-    quad(jj, 0, fa[r]);
-    rb[r] = ld(b + (size_t)jj * P);
-  }
-  Cd y1{0, 0}, y2{0, 0}, y3{0, 0}, y4{0, 0};
-#pragma unroll kUnrollRows
-  for (int j0 = 0; j0 < nm; j0 += kPf) {
-#pragma unroll
-    for (int r = 0; r < kPf; ++r) {
-      const int j = j0 + r;
-      if (j == tail_at && j > 0) load_tail();
-      if (j < nm) {
-        // oldest terms first: the newest value y1 enters last, so the
-        // row-to-row dependency is a single fused multiply-add
-        Cd y = rb[r];  // right side of row j (j0 is a multiple of kPf)
-        y = y - fa[r][0] * y4;
-        y = y - fa[r][1] * y3;
-        y = y - fa[r][2] * y2;
-        y = y - fa[r][3] * y1;
-        y4 = y3;
-        y3 = y2;
-        y2 = y1;
-        y1 = y;
-        C(j) = y;
-      }
-      const int jn = j + kPf < nm ? j + kPf : nm - 1;
-      quad(jn, 0, fa[r]);
-      rb[r] = ld(b + (size_t)jn * P);
-      // keep the source order: the loads of row jn go out now, not next to
-      // their use kPf rows later
-      if constexpr (NR > 0) __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int j = nm + r;
-    Cd y = rt[r];
-#pragma unroll
-    for (int t = 1; t <= 4; ++t) y = y - lt[r][4 - t] * C(j - t);
-    const int tt = n - 1 - j;
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-      if (c <= r) y = y - le[edge_off(tt) + c] * C(n - 9 + c);
-    C(j) = y;
-  }
-  // back substitution over rows N-1..4
-  if (head_at == n - 1) load_head();
-  double u[kPf][5];
-#pragma unroll
-  for (int r = 0; r < kPf; ++r) {
-    const int jj = n - 1 - r >= 4 ? n - 1 - r : 4;
-    u[r][0] = row(jj, 4);
-    quad(jj, 1, u[r] + 1);
-  }
-  Cd cb[kPc];
-#pragma unroll
-  for (int r = 0; r < kPc; ++r) cb[r] = C(n - 1 - r >= 4 ? n - 1 - r : 4);
-  Cd x1{0, 0}, x2{0, 0}, x3{0, 0}, x4{0, 0};
-#pragma unroll kUnrollRows
-  for (int j0 = n - 1; j0 >= 4; j0 -= kPf) {
-#pragma unroll
-    for (int r = 0; r < kPf; ++r) {
-      const int j = j0 - r;
-      if (j == head_at && j < n - 1) load_head();
-      if (j >= 4) {
-        const int i = r % kPc;  // = (n - 1 - j) mod kPc
-        Cd xv = cb[i];
-        xv = xv - u[r][4] * x4;
-        xv = xv - u[r][3] * x3;
-        xv = xv - u[r][2] * x2;
-        xv = xv - u[r][1] * x1;
-        xv = u[r][0] * xv;
-        x4 = x3;
-        x3 = x2;
-        x2 = x1;
-        x1 = xv;
-        C(j) = xv;
-        // row j - kPc still holds the forward result (written downwards)
-        const int jc = j - kPc >= 4 ? j - kPc : 4;
-        cb[i] = C(jc);
-      }
-      const int jn = j - kPf >= 4 ? j - kPf : 4;
-      u[r][0] = row(jn, 4);
-      quad(jn, 1, u[r] + 1);
-      // keep the source order: the loads of row jn go out now, not next to
-      // their use kPf rows later
-      if constexpr (NR > 0) __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-#pragma unroll
-  for (int r = 3; r >= 0; --r) {
-    Cd xv = C(r);
-#pragma unroll
-    for (int t = 1; t <= 4; ++t) xv = xv - ut[r][t] * C(r + t);
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-      if (c < 4 - r) xv = xv - ue[edge_off(r) + c] * C(r + 5 + c);
-    C(r) = ut[r][0] * xv;
-  }
-#pragma unroll kUnrollCol
-  for (int j = 0; j < n; ++j) st(x + (size_t)j * P, C(j));
+  lu_solve<Cd>(F, q * kp1 + ka, n, [&](int j) { return ld(b + (size_t)j * P); },
+               [&](int j) -> Cd & { return *reinterpret_cast<Cd *>(x + (size_t)j * P); });
 }
-
 
 // Velocity right sides in place of f: f_X - (grad p0)_X inside, wall values
 // on rows 0 and N-1; mode (0,0) solves u_theta directly (X+- = +-i u_theta).
@@ -1451,254 +1218,6 @@ k_adj_vel(Dims d, Grid g, Factors fv, Factors ft, const double2 *__restrict__ sx
   outr(n - 1) = Cd{0, 0};
 }
 
-// ---------------------------------------------------------------------------
-// Transposed sweeps with the column in LDS (one lane per (mode, system), 64
-// lanes per workgroup): A^T x = b with A = LU, i.e. U^T y = b upwards, then
-// L^T x = y downwards, in place in the lane's LDS column.  The boundary rows
-// (0..8 and N-9..N-1, with the envelope entries) read their factors up
-// front; the bulk rows read theirs kPfT rows ahead.
-// ---------------------------------------------------------------------------
-constexpr int kPfT = 8;
-
-template <int NR, class COL>
-__device__ __forceinline__ void sweep_t_lds(const Factors &F, int op, int nrt, COL C) {
-  const int n = NR > 0 ? NR : nrt;
-  constexpr int kUnrollRows = NR > 0 ? NR : 1;
-  const size_t nops = F.nops;
-  const double *__restrict__ vals = F.vals + op;
-  const double *__restrict__ edge = F.edge + op;
-  auto V = [&](int row, int slot) { return vals[((size_t)row * kSlots + slot) * nops]; };
-  // Unrolled: raw buffer loads (operator offset in one 32-bit register, row
-  // offset in a scalar register) of the packed rows (part 0: L row, 1: U
-  // row) and columns (2: L below the diagonal, 3: U above it), two 16-byte
-  // loads per part; else the compact rows.
-  const size_t n8 = (size_t)n * nops * sizeof(double);
-  const __amdgpu_buffer_rsrc_t rv = sweep_rsrc<NR>(F.vals, n8 * kSlots);
-  const __amdgpu_buffer_rsrc_t rk = sweep_rsrc<NR>(F.pk, n8 * 8);
-  const __amdgpu_buffer_rsrc_t rc = sweep_rsrc<NR>(F.pc, n8 * 8);
-  const int o8 = op * (int)sizeof(double);
-  auto dg = [&](int j) -> double {  // 1/U_jj
-    if constexpr (NR > 0)
-      return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(
-                                            rv, o8, (j * kSlots + 4) * (int)nops * 8, 0));
-    else
-      return V(j, 4);
-  };
-  auto quad = [&](int j, int part, double *o) {
-    if constexpr (NR > 0) {
-      const int so = (j * 2 + (part & 1)) * (int)nops * 32;
-      const __amdgpu_buffer_rsrc_t r = part < 2 ? rk : rc;
-      const double2 a = __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(r, 4 * o8, so, 0));
-      const double2 b = __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(r, 4 * o8 + 16, so, 0));
-      o[0] = a.x;
-      o[1] = a.y;
-      o[2] = b.x;
-      o[3] = b.y;
-    } else {
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-        o[t] = part == 0 ? V(j, t)
-             : part == 1 ? V(j, 5 + t)
-             : part == 2 ? V(j + t + 1, 3 - t)   // L(j + t + 1, j)
-                         : V(j - t - 1, 5 + t);  // U(j - t - 1, j)
-    }
-  };
-  // U^T y = b: rows 0..8 with the top envelope entries
-  {
-    double hu[9][5], he[10];
-#pragma unroll
-    for (int j = 0; j < 9; ++j) {  // U(j, j + t), t = 0 the inverse diagonal
-      hu[j][0] = dg(j);
-      quad(j, 1, hu[j] + 1);
-    }
-#pragma unroll
-    for (int e = 0; e < 10; ++e) he[e] = edge[(size_t)e * nops];
-#pragma unroll
-    for (int j = 0; j < 9; ++j) {
-      Cd y = C(j);
-#pragma unroll
-      for (int t = 1; t <= 4; ++t)
-        if (j - t >= 0) y = y - hu[j - t][t] * C(j - t);
-#pragma unroll
-      for (int c = 0; c <= 3; ++c)
-        if (j - c >= 5) y = y - he[edge_off(c) + j - c - 5] * C(c);
-      C(j) = hu[j][0] * y;
-    }
-  }
-  {
-    // bulk rows 9..N-1: the U column above row j (U(j - t, j) at t) and
-    // 1/U_jj at 0
-    double fa[kPfT][5];
-#pragma unroll
-    for (int r = 0; r < kPfT; ++r) {
-      const int j = 9 + r < n ? 9 + r : n - 1;
-      quad(j, 3, fa[r] + 1);
-      fa[r][0] = dg(j);
-    }
-    Cd y1 = C(8), y2 = C(7), y3 = C(6), y4 = C(5);
-#pragma unroll kUnrollRows
-    for (int j0 = 9; j0 < n; j0 += kPfT) {
-#pragma unroll
-      for (int r = 0; r < kPfT; ++r) {
-        const int j = j0 + r;
-        if (j < n) {
-          Cd y = C(j);
-          y = y - fa[r][4] * y4;
-          y = y - fa[r][3] * y3;
-          y = y - fa[r][2] * y2;
-          y = y - fa[r][1] * y1;
-          y = fa[r][0] * y;
-          y4 = y3;
-          y3 = y2;
-          y2 = y1;
-          y1 = y;
-          C(j) = y;
-        }
-        const int jn = j + kPfT < n ? j + kPfT : n - 1;
-        quad(jn, 3, fa[r] + 1);
-        fa[r][0] = dg(jn);
-      }
-    }
-  }
-  // L^T x = y: rows N-1..N-9 with the bottom envelope entries
-  {
-    double tl[9][4], te[10];
-#pragma unroll
-    for (int i = 0; i < 9; ++i) quad(n - 9 + i, 0, tl[i]);  // L(row, row - 4 + t)
-#pragma unroll
-    for (int e = 0; e < 10; ++e) te[e] = edge[(size_t)(10 + e) * nops];
-#pragma unroll
-    for (int i = 8; i >= 0; --i) {
-      const int j = n - 9 + i;
-      Cd x = C(j);
-#pragma unroll
-      for (int t = 1; t <= 4; ++t)
-        if (i + t <= 8) x = x - tl[i + t][4 - t] * C(j + t);  // L(j + t, j)
-#pragma unroll
-      for (int ci = 5; ci <= 8; ++ci) {
-        const int c = n - 9 + ci;  // rows N-4..N-1
-        if (ci - i >= 5) x = x - te[edge_off(n - 1 - c) + j - (n - 9)] * C(c);
-      }
-      C(j) = x;
-    }
-  }
-  {
-    // bulk rows N-10..0: the L column below row j (L(j + t, j) at t)
-    double fl[kPfT][5];
-#pragma unroll
-    for (int r = 0; r < kPfT; ++r) {
-      const int j = n - 10 - r >= 0 ? n - 10 - r : 0;
-      quad(j, 2, fl[r] + 1);
-    }
-    Cd x1 = C(n - 9), x2 = C(n - 8), x3 = C(n - 7), x4 = C(n - 6);
-#pragma unroll kUnrollRows
-    for (int j0 = n - 10; j0 >= 0; j0 -= kPfT) {
-#pragma unroll
-      for (int r = 0; r < kPfT; ++r) {
-        const int j = j0 - r;
-        if (j >= 0) {
-          Cd x = C(j);
-          x = x - fl[r][4] * x4;
-          x = x - fl[r][3] * x3;
-          x = x - fl[r][2] * x2;
-          x = x - fl[r][1] * x1;
-          x4 = x3;
-          x3 = x2;
-          x2 = x1;
-          x1 = x;
-          C(j) = x;
-        }
-        const int jn = j - kPfT >= 0 ? j - kPfT : 0;
-        quad(jn, 2, fl[r] + 1);
-      }
-    }
-  }
-}
-
-// k_adj_vel and k_adj_poisson with the LDS sweep: kind 0 the transposed
-// Helmholtz problems (blockIdx.y: 0/1/2 velocity +, -, z; 3 temperature),
-// kind 1 the transposed Poisson problem.  Same right sides and masks.
-template <int NR>
-__global__ void __launch_bounds__(kSweepLanes)
-k_adj_sweep(Dims d, Grid g, Factors fv, Factors ft, Factors fp, int kind,
-            const double2 *__restrict__ src, const double2 *__restrict__ bbar,
-            double2 *__restrict__ dst) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  Cd *col = reinterpret_cast<Cd *>(smem);
-  const int lane = threadIdx.x;
-  const int comp = blockIdx.y;
-  // the factor family depends only on the launch and the system, so that its
-  // base addresses stay uniform (scalar buffer resources)
-  const Factors F = kind == 1 ? fp : (comp == 3 ? ft : fv);
-  const int md = blockIdx.x * kSweepLanes + lane;
-  if (md >= d.nmodes) return;
-  const size_t P = d.nmodes;
-  const int n = NR > 0 ? NR : d.nr;
-  const int kp1 = d.kmax + 1;
-  const int m = md / d.mz;
-  const int kk = md - m * d.mz;
-  const int ka = kk >= d.kmax ? kk - d.kmax : d.kmax - kk;
-  const double kap = (double)(kk - d.kmax) * d.kz;
-  const bool zero = (m == 0 && ka == 0);
-  auto C = [&](int j) -> Cd & { return col[j * kSweepLanes + lane]; };
-  const double2 *xb = src + (size_t)(kind == 0 ? comp : 0) * n * P + md;
-  double2 *out = dst + (size_t)(kind == 0 ? comp : 0) * n * P + md;
-  int op = 0;
-  if (kind == 1) {
-    if (zero) {
-      for (int j = 0; j < n; ++j) st(out + (size_t)j * P, Cd{0, 0});
-      return;
-    }
-    op = m * kp1 + ka;
-    for (int j = 0; j < n; ++j) C(j) = ld(xb + (size_t)j * P);
-  } else if (comp == 3) {
-    op = m * kp1 + ka;
-    for (int j = 0; j < n; ++j) C(j) = ld(xb + (size_t)j * P);
-  } else if (zero) {
-    if (comp == 1) return;
-    op = (comp == 0 ? 1 : 0) * kp1 + ka;
-    for (int j = 0; j < n; ++j) C(j) = ld(xb + (size_t)j * P);
-  } else {
-    const int q = comp == 0 ? m + 1 : (comp == 1 ? (m >= 1 ? m - 1 : 1 - m) : m);
-    op = q * kp1 + ka;
-    const Cd b0 = ld(bbar + 2 * (size_t)md), b1 = ld(bbar + 2 * (size_t)md + 1);
-    const double sgn = comp == 0 ? 1.0 : -1.0;
-    for (int j = 0; j < n; ++j) {
-      Cd v = ld(xb + (size_t)j * P);
-      if (comp < 2) {
-        // 1/2 (D1 + (1 +- m)/r)^T e_w beta_bar_w
-        if (j <= 8) {
-          double c = g.d1[0 * kStencil + j];
-          if (j == 0) c += (1.0 + sgn * m) * g.rinv[0];
-          v = v + (0.5 * c) * b0;
-        }
-        if (j >= n - 9) {
-          double c = g.d1[(n - 1) * kStencil + (j - g.s[n - 1])];
-          if (j == n - 1) c += (1.0 + sgn * m) * g.rinv[n - 1];
-          v = v + (0.5 * c) * b1;
-        }
-      } else {
-        if (j == 0) v = v - kap * ci(b0);
-        if (j == n - 1) v = v - kap * ci(b1);
-      }
-      C(j) = v;
-    }
-  }
-  sweep_t_lds<NR>(F, op, n, C);
-  C(0) = Cd{0, 0};
-  C(n - 1) = Cd{0, 0};
-  if (kind == 0 && zero && comp == 0) {  // fbar+ = (i/2) rbar_theta, fbar- = -(i/2) rbar_theta
-    double2 *om = dst + (size_t)n * P + md;
-    for (int j = 0; j < n; ++j) {
-      const Cd h = 0.5 * ci(C(j));
-      st(out + (size_t)j * P, h);
-      st(om + (size_t)j * P, Cd{-h.x, -h.y});
-    }
-    return;
-  }
-  for (int j = 0; j < n; ++j) st(out + (size_t)j * P, C(j));
-}
-
 // pbar0 = -D1^T (rbar+ + rbar-) + (m/r)(rbar+ - rbar-) + i kappa rbar_z.
 __global__ void k_adj_pbar(Dims d, Grid g, const double2 *__restrict__ sf, double2 *__restrict__ pb) {
   const int md = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1976,52 +1495,32 @@ hipError_t launch_add_base(const nsc_ctx *c, const double *pert_tilde, double *o
 
 hipError_t launch_solve_vjp(const nsc_ctx *c, const double *ubar_out, double *ubar_n,
                             double *nbar_n, double *nbar_q, double dt, double cc,
-                            int overwrite) {
+                            int overwrite, double *scratch) {
+  if (c->fused_adj)
+    return launch_stage_adj(c, ubar_out, ubar_n, nbar_n, nbar_q, dt, cc, overwrite);
   const double2 *ub = reinterpret_cast<const double2 *>(ubar_out);
   double2 *sx = reinterpret_cast<double2 *>(c->s_x);
   double2 *sf = reinterpret_cast<double2 *>(c->s_f);
   double2 *sg = reinterpret_cast<double2 *>(c->s_g);
   double2 *sp = reinterpret_cast<double2 *>(c->s_p);
   double2 *lam = reinterpret_cast<double2 *>(c->s_lam);
+  double *nq = nbar_q ? nbar_q : scratch;
+  if (!nbar_q) overwrite |= 4;
   hipLaunchKernelGGL(k_adj_out, mode_grid(c, c->d.nr), dim3(256), 0, c->stream, c->d, ub, sx);
   hipLaunchKernelGGL(k_adj_lambda, dim3((c->d.nmodes + kLamModes - 1) / kLamModes), dim3(kLamModes * kLamParts),
                      0, c->stream, c->d, c->inf, sx, lam);
-  const size_t col_bytes = (size_t)kSweepLanes * c->d.nr * sizeof(Cd);
-  const bool lds = col_bytes <= 64 * 1024;
-  const dim3 lg((c->d.nmodes + kSweepLanes - 1) / kSweepLanes, c->d.heated ? 4 : 3);
-  const dim3 lg1((c->d.nmodes + kSweepLanes - 1) / kSweepLanes, 1);
-  // the unrolled sweeps read the packed factors (present where they run)
-  const bool unrolled = lds && c->fv.pc;
-  auto adj_sweep = c->d.nr == 64 ? k_adj_sweep<64> : k_adj_sweep<32>;
-  if (unrolled)
-    hipLaunchKernelGGL(adj_sweep, lg, dim3(kSweepLanes), col_bytes, c->stream, c->d, c->g,
-                       c->fv, c->ft, c->fp, 0, sx, lam, sf);
-  else if (lds)
-    hipLaunchKernelGGL(k_adj_sweep<0>, lg, dim3(kSweepLanes), col_bytes, c->stream, c->d, c->g,
-                       c->fv, c->ft, c->fp, 0, sx, lam, sf);
-  else
-    hipLaunchKernelGGL(k_adj_vel, mode_grid(c, c->d.heated ? 4 : 3), dim3(256), 0, c->stream, c->d,
-                       c->g, c->fv, c->ft, sx, lam, sf);
+  hipLaunchKernelGGL(k_adj_vel, mode_grid(c, c->d.heated ? 4 : 3), dim3(256), 0, c->stream, c->d,
+                     c->g, c->fv, c->ft, sx, lam, sf);
   hipLaunchKernelGGL(k_adj_pbar, mode_grid(c, c->d.nr), dim3(256), 0, c->stream, c->d, c->g, sf, sp);
-  if (unrolled)
-    hipLaunchKernelGGL(adj_sweep, lg1, dim3(kSweepLanes), col_bytes, c->stream, c->d, c->g,
-                       c->fv, c->ft, c->fp, 1, sp, lam, sg);
-  else if (lds)
-    hipLaunchKernelGGL(k_adj_sweep<0>, lg1, dim3(kSweepLanes), col_bytes, c->stream, c->d, c->g,
-                       c->fv, c->ft, c->fp, 1, sp, lam, sg);
-  else
-    hipLaunchKernelGGL(k_adj_poisson, mode_grid(c, 1), dim3(256), 0, c->stream, c->d, c->fp, sp, sg);
+  hipLaunchKernelGGL(k_adj_poisson, mode_grid(c, 1), dim3(256), 0, c->stream, c->d, c->fp, sp, sg);
   hipLaunchKernelGGL(k_adj_f, mode_grid(c, c->d.nr), dim3(256), 0, c->stream, c->d, c->g, sf, sg, sx);
   hipLaunchKernelGGL(k_adj_in, mode_grid(c, c->d.nr), dim3(256), 0, c->stream, c->d, c->g,
                      c->t_row, c->t_cnt, c->t_wt, sx, 1.0 / dt, cc,
                      reinterpret_cast<double2 *>(ubar_n), reinterpret_cast<double2 *>(nbar_n),
-                     reinterpret_cast<double2 *>(nbar_q), overwrite);
-  return hipGetLastError();
-}
-
-__global__ void k_fill_zero(double *__restrict__ p, size_t n) {
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-    p[i] = 0.0;
+                     reinterpret_cast<double2 *>(nq), overwrite);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || nbar_q) return e;
+  return launch_add(c, nbar_n, nq, (size_t)c->d.f * c->d.nr * c->d.nmodes * 2);
 }
 
 __global__ void k_add(double *__restrict__ y, const double *__restrict__ x, size_t n) {
@@ -2029,13 +1528,7 @@ __global__ void k_add(double *__restrict__ y, const double *__restrict__ x, size
     y[i] += x[i];
 }
 
-// n doubles set to zero / y += x, in kernels (no memset node when captured)
-hipError_t launch_fill_zero(const nsc_ctx *c, double *p, size_t n) {
-  const size_t blocks = (n + 255) / 256 < 65536 ? (n + 255) / 256 : 65536;
-  hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)blocks), dim3(256), 0, c->stream, p, n);
-  return hipGetLastError();
-}
-
+// y += x over n doubles
 hipError_t launch_add(const nsc_ctx *c, double *y, const double *x, size_t n) {
   const size_t blocks = (n + 255) / 256 < 65536 ? (n + 255) / 256 : 65536;
   hipLaunchKernelGGL(k_add, dim3((unsigned)blocks), dim3(256), 0, c->stream, y, x, n);
@@ -2058,22 +1551,9 @@ hipError_t launch_solve_sweeps(const nsc_ctx *c, int stage, const double *nn, co
   double2 *sp = reinterpret_cast<double2 *>(c->s_p);
   double2 *sx = reinterpret_cast<double2 *>(c->s_x);
   const int wp = (want_p && nn) ? 1 : 0;
-  const size_t col_bytes = (size_t)kSweepLanes * d.nr * sizeof(Cd);
-  const bool lds = col_bytes <= 64 * 1024;
-  const size_t shm = lds ? col_bytes : 0;
   auto launch = [&](const SweepArgs &a, int nsys, auto family) {
-    constexpr int FAM = decltype(family)::value;
     dim3 gr((d.nmodes + kSweepLanes - 1) / kSweepLanes, nsys);
-    // the unrolled variant reads the row-packed factors with 32-bit buffer
-    // offsets (allocated where sweeps_unrolled holds)
-    if (lds && c->fv.pk && d.nr == 64)
-      hipLaunchKernelGGL((k_sweep<true, FAM, 64>), gr, dim3(kSweepLanes), shm, c->stream, d, a);
-    else if (lds && c->fv.pk)
-      hipLaunchKernelGGL((k_sweep<true, FAM, 32>), gr, dim3(kSweepLanes), shm, c->stream, d, a);
-    else if (lds)
-      hipLaunchKernelGGL((k_sweep<true, FAM, 0>), gr, dim3(kSweepLanes), shm, c->stream, d, a);
-    else
-      hipLaunchKernelGGL((k_sweep<false, FAM, 0>), gr, dim3(kSweepLanes), 0, c->stream, d, a);
+    hipLaunchKernelGGL((k_sweep<decltype(family)::value>), gr, dim3(kSweepLanes), 0, c->stream, d, a);
   };
   const size_t fld = (size_t)d.nr * d.nmodes;
   if (stage == 0) {

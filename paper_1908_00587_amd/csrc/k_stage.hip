@@ -69,25 +69,26 @@ struct StageArgs {
   int walls, head;
 };
 
-// LDS layout in doubles: three fields, the edge entries E, then one region
+// LDS layout in doubles: the edge entries E, three fields, then one region
 // for the weight tables T1 and T2 and the factor chunks: T2 and the chunks of
 // the pressure and temperature sweeps behind T1, those of the velocity sweeps
 // from its start.  kc_*: rows per chunk (multiples of kBlock; the last chunk
 // brings the four rows past the band rows along).
 struct StageLds {
   int fs;  // field stride, complex
-  int e, t1, t2, total, kc_pt, kc_v;
+  int f, t1, t2, total, kc_pt, kc_v;
 };
 
-// rows n, RPT rows per thread, npt pressure and temperature systems; budget in
-// doubles.  total > budget if even the smallest chunks do not fit.
+// rows n, rpt rows per thread, npt pressure and temperature systems, stencil
+// windows of rpt + extra rows, one weight table or two; budget in doubles.  total > budget if even the smallest chunks do not fit.
 template <int OPS>
-StageLds stage_lds(int n, int rpt, int npt, int budget) {
+StageLds stage_lds(int n, int rpt, int npt, int extra, bool two, int budget) {
   StageLds l;
-  const int nw = ((n + rpt - 1) / rpt * rpt * (rpt + 8) + 1) & ~1;  // one table of padded weights
+  // one table of padded weights (windows of rpt + extra rows)
+  const int nw = ((n + rpt - 1) / rpt * rpt * (rpt + extra) + 1) & ~1;
   l.fs = n * 2 * OPS + kPad;
-  l.e = 2 * 3 * l.fs;
-  l.t1 = l.e + 3 * kEdge * OPS;
+  l.f = 3 * kEdge * OPS;
+  l.t1 = l.f + 2 * 3 * l.fs;
   l.t2 = l.t1 + nw;
   const int most = (n - 4 + kBlock - 1) / kBlock * kBlock;
   auto rows = [&](int room, int ns) {
@@ -97,7 +98,7 @@ StageLds stage_lds(int n, int rpt, int npt, int budget) {
   };
   l.kc_pt = rows(budget - l.t2, npt);
   l.kc_v = rows(budget - l.t1, 3);
-  const int a = l.t2 + nw, b = l.t2 + (l.kc_pt + 4) * npt * OPS * 5, c = l.t1 + (l.kc_v + 4) * 3 * OPS * 5;
+  const int a = l.t2 + (two ? nw : 0), b = l.t2 + (l.kc_pt + 4) * npt * OPS * 5, c = l.t1 + (l.kc_v + 4) * 3 * OPS * 5;
   l.total = a > b ? a : b;
   if (c > l.total) l.total = c;
   return l;
@@ -126,9 +127,12 @@ __device__ __forceinline__ void fill_weights(double *dst, const double *__restri
 
 // Stencil sums of NF fields over the thread's RPT rows: acc[f][jj] =
 // sum_e w[j0 + jj][e] x_f[base + e], from the left.
-template <int OPS, int RPT, int NF>
-__device__ __forceinline__ void stencil(const double *w, const Cd *x, int fs, Cd (&acc)[NF][RPT]) {
-  constexpr int W = RPT + 8;
+// (last: the window's last row inside the column, for the transposed windows
+// of single rows, which a short column does not fill)
+template <int OPS, int RPT, int NF, int EXTRA = 8>
+__device__ __forceinline__ void stencil(const double *w, const Cd *x, int fs, Cd (&acc)[NF][RPT],
+                                        int last = 0) {
+  constexpr int W = RPT + EXTRA;
 #pragma unroll
   for (int f = 0; f < NF; ++f)
 #pragma unroll
@@ -139,7 +143,8 @@ __device__ __forceinline__ void stencil(const double *w, const Cd *x, int fs, Cd
   double wt[2][RPT];
   auto load = [&](int e) {
 #pragma unroll
-    for (int f = 0; f < NF; ++f) v[e & 1][f] = x[f * fs + e * 2 * OPS];
+    for (int f = 0; f < NF; ++f)
+      v[e & 1][f] = x[f * fs + (EXTRA == 16 && e > last ? last : e) * 2 * OPS];
 #pragma unroll
     for (int jj = 0; jj < RPT; ++jj) wt[e & 1][jj] = w[jj * W + e];
   };
@@ -161,6 +166,20 @@ __device__ __forceinline__ void stencil(const double *w, const Cd *x, int fs, Cd
     for (int jj = 0; jj < RPT; ++jj) asm volatile("" : "+v"(acc[f][jj].x), "+v"(acc[f][jj].y));
 }
 
+// Row of the matrix at sweep index i (indices past the last repeat it), and
+// the lowest row of the indices [i rows, (i + 1) rows): a scalar base from
+// which the lanes' rows are a 32-bit byte offset away.
+template <bool DOWN>
+__device__ __forceinline__ int lane_row(int i, int n) {
+  i = i < n ? i : n - 1;
+  return DOWN ? n - 1 - i : i;
+}
+template <bool DOWN>
+__device__ __forceinline__ int first_row(int i, int rows, int n) {
+  const int r = DOWN ? n - (i + 1) * rows : i * rows;
+  return r < 0 ? 0 : (r < n ? r : n - 1);
+}
+
 // The factors of NS systems on the way from HBM to the sweeps: this thread's
 // share of the L or U rows, the inverse diagonals, and the edge entries, in
 // registers.
@@ -172,31 +191,32 @@ struct FactorRegs {
   double ed[NS];
 
   // system s: op0 the tile's first operator (ops past the last live one
-  // repeat it).  Rows in sweep order: the L rows upwards, the U rows
-  // (BACK) downwards from n - 1.
-  template <bool BACK>
+  // repeat it).  The L rows (or, UP, the U rows with the inverse diagonals) in
+  // sweep order: upwards, or DOWN from n - 1.
+  template <bool UP, bool DOWN>
   __device__ __forceinline__ void load(int s, const Factors &F, int op0, int nlive, int n, int t) {
     {
       const int o = (t / 2) % OPS;
       const unsigned col = (unsigned)(o < nlive ? o : nlive - 1) * 32 + 16 * (t & 1);
-      const double *p = F.pk + ((size_t)(BACK ? 1 : 0) * F.nops + op0) * 4;
+      constexpr int RQ = kStageThreads / (2 * OPS);  // rows per register
 #pragma unroll
       for (int i = 0; i < RPT; ++i) {
-        int row = t / (2 * OPS) + i * (kStageThreads / (2 * OPS));
-        row = row < n ? row : n - 1;
-        if (BACK) row = n - 1 - row;
-        q[s][i] = at<Dbl2>(p, (unsigned)row * ((unsigned)F.nops * 64) + col);
+        const int r0 = first_row<DOWN>(i, RQ, n);
+        const double *p = F.pk + (((size_t)r0 * 2 + (UP ? 1 : 0)) * F.nops + op0) * 4;
+        q[s][i] = at<Dbl2>(p, (unsigned)(lane_row<DOWN>(t / (2 * OPS) + i * RQ, n) - r0) *
+                                  ((unsigned)F.nops * 64) + col);
       }
     }
-    if (BACK) {
+    if (UP) {
+      constexpr int RD = kStageThreads / OPS;
       const int o = t % OPS;
       const unsigned col = (unsigned)(o < nlive ? o : nlive - 1) * 8;
-      const double *p = F.vals + 4 * (size_t)F.nops + op0;
 #pragma unroll
       for (int i = 0; i < DQ; ++i) {
-        int row = t / OPS + i * (kStageThreads / OPS);
-        row = row < n ? row : n - 1;
-        dg[s][i] = at<double>(p, (unsigned)(n - 1 - row) * ((unsigned)F.nops * (8 * kSlots)) + col);
+        const int r0 = first_row<DOWN>(i, RD, n);
+        const double *p = F.vals + ((size_t)r0 * kSlots + 4) * F.nops + op0;
+        dg[s][i] = at<double>(p, (unsigned)(lane_row<DOWN>(t / OPS + i * RD, n) - r0) *
+                                     ((unsigned)F.nops * (8 * kSlots)) + col);
       }
     }
   }
@@ -211,8 +231,8 @@ struct FactorRegs {
       if (t < kEdge * OPS) E[s * kEdge * OPS + t] = ed[s];
   }
   // rows [r0, r1) of the sweep order to B[row - r0][system][op][4], the
-  // diagonals (BACK) to D[row - r0][system][op]
-  template <bool BACK>
+  // diagonals (UP) to D[row - r0][system][op]
+  template <bool UP>
   __device__ __forceinline__ void store_rows(double *B, double *D, int r0, int r1, int t) const {
     constexpr int RQ = kStageThreads / (2 * OPS), RD = kStageThreads / OPS;  // rows per register
 #pragma unroll
@@ -223,7 +243,7 @@ struct FactorRegs {
         for (int s = 0; s < NS; ++s)
           *reinterpret_cast<Dbl2 *>(B + ((row - r0) * NS + s) * (4 * OPS) + 2 * (t % (2 * OPS))) = q[s][i];
     }
-    if (BACK) {
+    if (UP) {
 #pragma unroll
       for (int i = 0; i < DQ; ++i) {
         const int row = t / OPS + i * RD;
@@ -396,8 +416,8 @@ __global__ void __launch_bounds__(kStageThreads, 2) k_stage(Dims d, Grid g, Stag
   constexpr int NPT = HEATED ? 2 : 1;
   const int n = d.nr, K = d.kmax, kp1 = K + 1;
   double *base = reinterpret_cast<double *>(smem);
-  Cd *fA = reinterpret_cast<Cd *>(smem), *fB = fA + lay.fs, *fC = fB + lay.fs;
-  double *T1 = base + lay.t1, *S = base + lay.t2, *E = base + lay.e;
+  double *E = base, *fld = base + lay.f, *T1 = base + lay.t1, *S = base + lay.t2;
+  Cd *fA = reinterpret_cast<Cd *>(fld), *fB = fA + lay.fs, *fC = fB + lay.fs;
   const int t = threadIdx.x;
   // neighbouring |k| tiles share cache lines: contiguous tiles per XCD
   // (spans of 16 |k| with m next, for the factors that q = m, m + 1 share,
@@ -523,10 +543,10 @@ __global__ void __launch_bounds__(kStageThreads, 2) k_stage(Dims d, Grid g, Stag
   // the pressure and temperature factors come next
   FactorRegs<OPS, NPT, RPT> L1, U1;
   const int opm = m * kp1 + ka0;
-  L1.template load<false>(0, a.fp, opm, nlive, n, t);
+  L1.template load<false, false>(0, a.fp, opm, nlive, n, t);
   L1.load_edges(0, a.fp, opm, nlive, t);
   if constexpr (HEATED) {
-    L1.template load<false>(NPT - 1, a.ft, opm, nlive, n, t);
+    L1.template load<false, false>(NPT - 1, a.ft, opm, nlive, n, t);
     L1.load_edges(NPT - 1, a.ft, opm, nlive, t);
   }
   __syncthreads();
@@ -588,18 +608,18 @@ __global__ void __launch_bounds__(kStageThreads, 2) k_stage(Dims d, Grid g, Stag
   if (PIPE) fill_weights<RPT>(T1, wd + odd_off(g, m), n, t);
   // ---- pressure and temperature sweeps (their U rows on their way)
   const int op_v[3] = {(m + 1) * kp1 + ka0, (m >= 1 ? m - 1 : 1) * kp1 + ka0, opm};
-  U1.template load<true>(0, a.fp, opm, nlive, n, t);
+  U1.template load<true, true>(0, a.fp, opm, nlive, n, t);
   if constexpr (HEATED) {
-    U1.template load<true>(NPT - 1, a.ft, opm, nlive, n, t);
+    U1.template load<true, true>(NPT - 1, a.ft, opm, nlive, n, t);
   }
-  sweep_dir<false, OPS, NPT, RPT>(L1, base, lay.fs, S, lay.kc_pt, E, n, t);
-  sweep_dir<true, OPS, NPT, RPT>(U1, base, lay.fs, S, lay.kc_pt, E, n, t);
+  sweep_dir<false, OPS, NPT, RPT>(L1, fld, lay.fs, S, lay.kc_pt, E, n, t);
+  sweep_dir<true, OPS, NPT, RPT>(U1, fld, lay.fs, S, lay.kc_pt, E, n, t);
   // ---- temperature out; velocity right sides f - grad p0 (the velocity L
   // rows on their way)
   FactorRegs<OPS, 3, RPT> L2;
 #pragma unroll
   for (int s = 0; s < 3; ++s) {
-    L2.template load<false>(s, a.fv, op_v[s], nlive, n, t);
+    L2.template load<false, false>(s, a.fv, op_v[s], nlive, n, t);
     L2.load_edges(s, a.fv, op_v[s], nlive, t);
   }
   Cd p0[RPT];
@@ -650,9 +670,9 @@ __global__ void __launch_bounds__(kStageThreads, 2) k_stage(Dims d, Grid g, Stag
   FactorRegs<OPS, 3, RPT> U2;
 #pragma unroll
   for (int s = 0; s < 3; ++s) {
-    U2.template load<true>(s, a.fv, op_v[s], nlive, n, t);
+    U2.template load<true, true>(s, a.fv, op_v[s], nlive, n, t);
   }
-  sweep_dir<false, OPS, 3, RPT>(L2, base, lay.fs, T1, lay.kc_v, E, n, t);
+  sweep_dir<false, OPS, 3, RPT>(L2, fld, lay.fs, T1, lay.kc_v, E, n, t);
   Dbl2 rs[WITH_P ? 4 : 3][RPT];
   const int opi = m * kp1 + ka;
 #pragma unroll
@@ -666,7 +686,7 @@ __global__ void __launch_bounds__(kStageThreads, 2) k_stage(Dims d, Grid g, Stag
     rs[2][jj] = R(3);
     if constexpr (WITH_P) rs[WITH_P ? 3 : 0][jj] = R(0);
   }
-  sweep_dir<true, OPS, 3, RPT>(U2, base, lay.fs, T1, lay.kc_v, E, n, t);
+  sweep_dir<true, OPS, 3, RPT>(U2, fld, lay.fs, T1, lay.kc_v, E, n, t);
   // ---- lambda = -A^-1 beta(X0), beta the wall divergences: one lane per
   // (wall, mode); S is free again
   Cd *lam = reinterpret_cast<Cd *>(S);
@@ -729,6 +749,465 @@ __global__ void __launch_bounds__(kStageThreads, 2) k_stage(Dims d, Grid g, Stag
   }
 }
 
+// ---------------------------------------------------------------------------
+// Vector--Jacobian product of the implicit stage in one kernel: the
+// conjugate transposes of the steps above in reverse order (formulas at the
+// kernel sequence in k_solve.hip), on the same tiles. What bounds it is what
+// bounds k_stage, the serial sweeps (here in axpy form: the rows of the packed
+// factors are the columns of their transposes, so no second copy of the factors
+// is kept) between barriers. It replaces eight to ten launches that passed the
+// fields through memory. Per call, sequence -> this kernel: 32x16x15 61 -> 24 us,
+// 64x32x63 98 -> 49, 64x64x127 heated 211 -> 146, 128x64x127 653 -> 279,
+// 128x64x127 heated 725 -> 368.
+// ---------------------------------------------------------------------------
+
+// Rows past RPT of the window that holds, for every column of a group of RPT
+// rows, the rows whose nine-point windows contain it: nine inside, up to
+// thirteen next to the one-sided wall windows, and up to all of them in
+// columns of up to 18 points, where the two walls' windows overlap (taken
+// with one row per thread there: stage_shape).
+constexpr int win_extra_t(int rpt) { return rpt == 1 ? 16 : 12; }
+
+// First row of that window for the group from j0 on.
+template <int RPT>
+__device__ __forceinline__ int win_base_t(int j0, int n) {
+  const int hi = n - (RPT + win_extra_t(RPT));
+  return clampi(j0 <= 8 ? 0 : j0 - 4, 0, hi > 0 ? hi : 0);
+}
+
+// Transposed weight table: dst[j][RPT + win_extra_t], entry e the weight of row
+// base + e in column j.
+template <int RPT>
+__device__ __forceinline__ void fill_weights_t(double *dst, const double *__restrict__ w, int n, int t) {
+  constexpr int W = RPT + win_extra_t(RPT);
+  const int rows = (n + RPT - 1) / RPT * RPT;
+  for (int i = t; i < rows * W; i += kStageThreads) {
+    const int j = i / W, e = i - j * W;
+    const int r = e + win_base_t<RPT>(j / RPT * RPT, n);
+    const int tt = j - clampi(r - 4, 0, n - kStencil);
+    dst[i] = j < n && r < n && tt >= 0 && tt < kStencil ? w[r * kStencil + tt] : 0.0;
+  }
+}
+
+// Partial sums of the next four rows of a transposed recurrence.
+struct CarryT {
+  double s0, s1, s2, s3;
+};
+
+// A transposed recurrence, rows in sweep order: U^T y = b upwards (UP), L^T x
+// = y downwards.  Row j's entries update the following rows as soon as its
+// value is known (four independent multiply-adds), so the factors are read by
+// rows here too; every row still takes its terms from the farthest to the
+// nearest.
+template <int OPS, bool UP, int NS>
+struct RecurT {
+  static constexpr int cs = UP ? 4 * OPS : -4 * OPS;
+  static constexpr int qs = NS * 4 * OPS, ds = NS * OPS;
+  // (b: the right side four rows on; past the last row it is never used)
+  __device__ __forceinline__ static Row row(const double *c, const double *S, const double *D, int i) {
+    Row r;
+    r.qa = *reinterpret_cast<const Dbl2 *>(S + i * qs);
+    r.qb = *reinterpret_cast<const Dbl2 *>(S + i * qs + 2);
+    r.b = c[(i + 4) * cs];
+    r.dg = UP ? D[i * ds] : 0.0;
+    return r;
+  }
+  __device__ __forceinline__ static double e(const Row &r, int d) {
+    return UP ? (d == 1 ? r.qa.x : d == 2 ? r.qa.y : d == 3 ? r.qb.x : r.qb.y)
+              : (d == 1 ? r.qb.y : d == 2 ? r.qb.x : d == 3 ? r.qa.y : r.qa.x);
+  }
+  __device__ __forceinline__ static void step(const Row &r, CarryT &k, double *c) {
+    const double y = UP ? k.s0 * r.dg : k.s0;
+    k.s0 = fma(-e(r, 1), y, k.s1);
+    k.s1 = fma(-e(r, 2), y, k.s2);
+    k.s2 = fma(-e(r, 3), y, k.s3);
+    k.s3 = fma(-e(r, 4), y, r.b);
+    *c = y;
+  }
+  template <int LEN, int R>
+  __device__ __forceinline__ static void rows(Row (&w)[R], CarryT &k, double *c, const double *S,
+                                              const double *D, bool more) {
+    static_assert(LEN % R == 0, "whole rings");
+#pragma unroll
+    for (int i = 0; i < LEN; ++i) {
+      step(w[i % R], k, c + i * cs);
+      if (i + R < LEN || more) w[i % R] = row(c, S, D, i + R);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  // The first four rows, whose envelope entries (E, stride OPS) reach past
+  // the band: row 0 + q (UP) to columns up to 8, row n-1-q down to n-9.
+  __device__ __forceinline__ static CarryT head(double *c, const double *S, const double *D,
+                                                const double *E) {
+    Row w[4];
+    double ed[10], b[9];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[i] = row(c, S, D, i);
+#pragma unroll
+    for (int t = 0; t < 10; ++t) ed[t] = E[((UP ? 0 : 10) + t) * OPS];
+#pragma unroll
+    for (int i = 0; i < 9; ++i) b[i] = c[i * cs];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const double y = UP ? b[q] * w[q].dg : b[q];
+#pragma unroll
+      for (int d = 1; d <= 4; ++d) b[q + d] = fma(-e(w[q], d), y, b[q + d]);
+#pragma unroll
+      for (int t = 0; t < 4 - q; ++t) {  // entry t: column q+5+t upwards, n-9+t downwards
+        const int i = UP ? q + 5 + t : 8 - t;
+        b[i] = fma(-ed[edge_off(q) + t], y, b[i]);
+      }
+      c[q * cs] = y;
+    }
+    c[8 * cs] = b[8];
+    return CarryT{b[4], b[5], b[6], b[7]};
+  }
+};
+
+// One direction of the transposed sweeps of NS systems (see sweep_dir).
+template <bool UP, int OPS, int NS, int RPT>
+__device__ __forceinline__ void sweep_dir_t(const FactorRegs<OPS, NS, RPT> &R, double *fld, int fs,
+                                            double *S, int kc, const double *E, int n, int t) {
+  using Q = RecurT<OPS, UP, NS>;
+  constexpr int kCols = 4 * OPS;
+  const int nb = n - 4;  // rows after the first four, which the first chunk brings along
+  const int sys = t / kCols, col = t % kCols, o = (col >> 1) % OPS;
+  const bool lane = t < NS * kCols;
+  double *c0 = fld + (size_t)sys * 2 * fs + col + (UP ? 0 : (n - 1) * kCols);
+  double *D = S + (kc + 4) * Q::qs;
+  const double *Sl = S + sys * 4 * OPS + o * 4, *Dl = D + sys * OPS + o;
+  const double *El = E + sys * kEdge * OPS + o;
+  CarryT k{0.0, 0.0, 0.0, 0.0};
+  for (int i0 = 0; i0 < nb; i0 += kc) {
+    const int first = i0 == 0 ? 0 : i0 + 4;  // chunk's first row
+    const int len = nb - i0 < kc ? nb - i0 : kc;
+    R.template store_rows<UP>(S, D, first, i0 + 4 + len, t);
+    __syncthreads();
+    if (lane) {
+      const double *Sc = Sl, *Dc = Dl;
+      if (i0 == 0) {
+        k = Q::head(c0, Sl, Dl, El);
+        Sc += 4 * Q::qs;
+        Dc += 4 * Q::ds;
+      }
+      double *c = c0 + (i0 + 4) * Q::cs;
+      int i = 0;
+      if (len >= kBlock) {
+        Row w[kRing];
+#pragma unroll
+        for (int r = 0; r < kRing; ++r) w[r] = Q::row(c, Sc, Dc, r);
+        __builtin_amdgcn_sched_barrier(0);
+        for (; i + kBlock <= len; i += kBlock)
+          Q::template rows<kBlock>(w, k, c + i * Q::cs, Sc + i * Q::qs, Dc + i * Q::ds,
+                                   i + 2 * kBlock <= len);
+      }
+      for (; i + 4 <= len; i += 4) {
+        Row w[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) w[r] = Q::row(c + i * Q::cs, Sc + i * Q::qs, Dc + i * Q::ds, r);
+        Q::template rows<4>(w, k, c + i * Q::cs, Sc + i * Q::qs, Dc + i * Q::ds, false);
+      }
+      for (; i < len; ++i) {
+        const Row w = Q::row(c + i * Q::cs, Sc + i * Q::qs, Dc + i * Q::ds, 0);
+        Q::step(w, k, c + i * Q::cs);
+      }
+    }
+    __syncthreads();
+  }
+}
+
+struct StageAdjArgs {
+  Factors fp, fv, ft;
+  Influence inf;
+  const double2 *ub;            // output adjoint
+  double2 *ubn, *nbn, *nbq;     // input adjoints (nbq null: its part is added to nbn)
+  double idt, cc;
+  int overwrite;                // bit 1 ubn, 2 nbn, 4 nbq written instead of accumulated
+};
+
+template <int OPS, int RPT, bool HEATED>
+__global__ void __launch_bounds__(kStageThreads, 2) k_stage_adj(Dims d, Grid g, StageAdjArgs a, StageLds lay) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr int X = win_extra_t(RPT), W = RPT + X;
+  constexpr int kModes = 2 * OPS;
+  constexpr int NPT = HEATED ? 2 : 1;
+  const int n = d.nr, K = d.kmax, kp1 = K + 1;
+  double *base = reinterpret_cast<double *>(smem);
+  double *E = base, *fld = base + lay.f, *T1 = base + lay.t1, *S = base + lay.t2;
+  Cd *fA = reinterpret_cast<Cd *>(fld), *fB = fA + lay.fs, *fC = fB + lay.fs;
+  const int t = threadIdx.x;
+  const int kt = (kp1 + OPS - 1) / OPS;
+  const int L = xcd_remap(blockIdx.x, gridDim.x);
+  const int m = L / kt, ka0 = (L - m * kt) * OPS;
+  const int nlive = kp1 - ka0 < OPS ? kp1 - ka0 : OPS;
+  const int ml = t % kModes, rg = t / kModes;
+  const int o = ml % OPS, sg = ml / OPS;
+  const int ka = ka0 + (o < nlive ? o : nlive - 1);
+  const int kk = sg ? K - ka : K + ka;
+  const bool live = o < nlive && !(sg && ka == 0);
+  const bool zero = m == 0 && ka == 0;
+  const int md = m * d.mz + kk;
+  const size_t fst = (size_t)n * d.nmodes;
+  const double kap = (double)(kk - K) * d.kz;
+  const double k2 = kap * kap, mm = (double)m;
+  const double ce = 1.0 - a.cc;
+  const int j0 = rg * RPT;
+  const int wb = win_base_t<RPT>(j0 < n ? j0 : n - 1, n);
+  const Cd *win = fA + wb * kModes + ml;
+  const int jw = j0 < n ? j0 : 0;
+  auto rowc = [&](int jj) { return j0 + jj < n ? j0 + jj : n - 1; };
+  auto ok = [&](int jj) { return j0 + jj < n; };
+  auto inner = [&](int j) { return j > 0 && j < n - 1; };
+  const unsigned row16 = (unsigned)d.nmodes * 16, md16 = (unsigned)md * 16;
+  auto off = [&](int jj) { return (unsigned)rowc(jj) * row16 + md16; };
+  const int opm = m * kp1 + ka0, opi = m * kp1 + ka;
+  const int op_v[3] = {(m + 1) * kp1 + ka0, (m >= 1 ? m - 1 : 1) * kp1 + ka0, opm};
+  // ---- output adjoint: m = 0 Hermitian, +- basis (mode (0,0): u_theta in
+  // the first slot)
+  Cd xp[RPT], xm[RPT], xz[RPT];
+#pragma unroll
+  for (int jj = 0; jj < RPT; ++jj) {
+    xp[jj] = ldc(a.ub, off(jj));
+    xm[jj] = ldc(a.ub + fst, off(jj));
+    xz[jj] = ldc(a.ub + 2 * fst, off(jj));
+  }
+  // ---- lambda_bar_w = sum_j (X_w+ Xbar+ + X_w- Xbar- + i kappa h_w Xbar_z)
+  Cd l1 = {0.0, 0.0}, l2 = {0.0, 0.0};
+#pragma unroll
+  for (int jj = 0; jj < RPT; ++jj) {
+    if (m == 0) {
+      xp[jj] = herm_pair<OPS>(xp[jj]);
+      xm[jj] = herm_pair<OPS>(xm[jj]);
+      xz[jj] = herm_pair<OPS>(xz[jj]);
+    }
+    const Cd r = xp[jj], th = xm[jj];
+    const Cd p = 0.5 * (r + ci(th)), q = 0.5 * (r - ci(th));
+    xp[jj] = Cd{zero ? th.x : p.x, zero ? th.y : p.y};
+    xm[jj] = Cd{zero ? 0.0 : q.x, zero ? 0.0 : q.y};
+    auto R = [&](int kind) {
+      return at<Dbl2>(a.inf.resp + (size_t)kind * n * a.inf.nops,
+                      ((unsigned)rowc(jj) * (unsigned)a.inf.nops + (unsigned)opi) * 16);
+    };
+    const Dbl2 r1 = R(1), r2 = R(2), r3 = R(3);
+    const Cd iz = kap * ci(xz[jj]);
+    const double on = ok(jj) ? 1.0 : 0.0;
+    l1 = l1 + on * (r1.x * xp[jj] + r2.x * xm[jj] + r3.x * iz);
+    l2 = l2 + on * (r1.y * xp[jj] + r2.y * xm[jj] + r3.y * iz);
+  }
+  FactorRegs<OPS, 3, RPT> U2;
+#pragma unroll
+  for (int s = 0; s < 3; ++s) {
+    U2.template load<true, false>(s, a.fv, op_v[s], nlive, n, t);
+    U2.load_edges(s, a.fv, op_v[s], nlive, t);
+  }
+  // over the row groups of a wavefront, then over the four wavefronts
+#pragma unroll
+  for (int msk = kModes; msk < 64; msk *= 2) {
+    l1 = l1 + Cd{xor_lane(l1.x, msk), xor_lane(l1.y, msk)};
+    l2 = l2 + Cd{xor_lane(l2.x, msk), xor_lane(l2.y, msk)};
+  }
+  Cd *red = reinterpret_cast<Cd *>(S);
+  if ((t & 63) < kModes) {
+    red[(t >> 6) * 2 * kModes + ml] = l1;
+    red[((t >> 6) * 2 + 1) * kModes + ml] = l2;
+  }
+  U2.store_edges(E, t);
+  __syncthreads();
+  l1 = red[ml];
+  l2 = red[kModes + ml];
+#pragma unroll
+  for (int w = 1; w < kStageThreads / 64; ++w) {
+    l1 = l1 + red[2 * w * kModes + ml];
+    l2 = l2 + red[(2 * w + 1) * kModes + ml];
+  }
+  // ---- right sides of the transposed Helmholtz problems: Xbar + the wall
+  // divergences' transposes times beta_bar = -A^-T lambda_bar
+  {
+    const size_t ns = a.inf.nops;
+    const double a00 = a.inf.ainv[opi], a01 = a.inf.ainv[ns + opi], a10 = a.inf.ainv[2 * ns + opi],
+                 a11 = a.inf.ainv[3 * ns + opi];
+    const double on = zero ? 0.0 : 1.0;
+    const Cd b0 = on * Cd{-(a00 * l1.x + a10 * l2.x), -(a00 * l1.y + a10 * l2.y)};
+    const Cd b1 = on * Cd{-(a01 * l1.x + a11 * l2.x), -(a01 * l1.y + a11 * l2.y)};
+    const double ri0 = g.rinv[0], ri1 = g.rinv[n - 1];
+#pragma unroll
+    for (int jj = 0; jj < RPT; ++jj) {
+      const int j = rowc(jj);
+      const double c0 = j <= 8 ? g.d1[j] : 0.0;
+      const double c1 = j >= n - 9 ? g.d1[(n - 1) * kStencil + (j - (n - 9))] : 0.0;
+      const double e0 = j == 0 ? ri0 : 0.0, e1 = j == n - 1 ? ri1 : 0.0;
+      const double z0 = j == 0 ? kap : 0.0, z1 = j == n - 1 ? kap : 0.0;
+      const Cd vp = xp[jj] + (0.5 * (c0 + (1.0 + mm) * e0)) * b0 + (0.5 * (c1 + (1.0 + mm) * e1)) * b1;
+      const Cd vm = xm[jj] + (0.5 * (c0 + (1.0 - mm) * e0)) * b0 + (0.5 * (c1 + (1.0 - mm) * e1)) * b1;
+      const Cd vz = xz[jj] - z0 * ci(b0) - z1 * ci(b1);
+      if (ok(jj)) {
+        const int pos = j * kModes + ml;
+        fA[pos] = vp;
+        fB[pos] = vm;
+        fC[pos] = vz;
+      }
+    }
+  }
+  __syncthreads();  // (the partial sums in S are read)
+  // ---- transposed velocity sweeps; their L rows on their way
+  FactorRegs<OPS, 3, RPT> L2;
+#pragma unroll
+  for (int s = 0; s < 3; ++s) L2.template load<false, true>(s, a.fv, op_v[s], nlive, n, t);
+  sweep_dir_t<true, OPS, 3, RPT>(U2, fld, lay.fs, T1, lay.kc_v, E, n, t);
+  FactorRegs<OPS, NPT, RPT> U1;
+  U1.template load<true, false>(0, a.fp, opm, nlive, n, t);
+  U1.load_edges(0, a.fp, opm, nlive, t);
+  if constexpr (HEATED) {
+    U1.template load<true, false>(NPT - 1, a.ft, opm, nlive, n, t);
+    U1.load_edges(NPT - 1, a.ft, opm, nlive, t);
+  }
+  sweep_dir_t<false, OPS, 3, RPT>(L2, fld, lay.fs, T1, lay.kc_v, E, n, t);
+  // ---- wall rows masked; mode (0,0): fbar+- = +-(i/2) rbar_theta
+  Cd rp[RPT], rm[RPT];
+#pragma unroll
+  for (int jj = 0; jj < RPT; ++jj) {
+    const int j = rowc(jj), pos = j * kModes + ml;
+    const Cd h = 0.5 * ci(fA[pos]);
+    Cd vp = fA[pos], vm = fB[pos], vz = fC[pos];
+    vp = Cd{zero ? h.x : vp.x, zero ? h.y : vp.y};
+    vm = Cd{zero ? -h.x : vm.x, zero ? -h.y : vm.y};
+    rp[jj] = Cd{inner(j) ? vp.x : 0.0, inner(j) ? vp.y : 0.0};
+    rm[jj] = Cd{inner(j) ? vm.x : 0.0, inner(j) ? vm.y : 0.0};
+    vz = Cd{inner(j) ? vz.x : 0.0, inner(j) ? vz.y : 0.0};
+    if (ok(jj)) {  // (this thread's own entries)
+      fA[pos] = rp[jj];
+      fB[pos] = rm[jj];
+      fC[pos] = vz;
+    }
+  }
+  fill_weights_t<RPT>(T1, g.d1, n, t);
+  U1.store_edges(E, t);
+  __syncthreads();
+  // ---- pbar0 = -D1^T (rbar+ + rbar-) + (m/r)(rbar+ - rbar-) + i kappa rbar_z
+  Cd tT[RPT];
+  {
+    Cd dv[2][RPT];
+    if constexpr (HEATED)
+#pragma unroll
+      for (int jj = 0; jj < RPT; ++jj) tT[jj] = ldc(a.ub + 3 * fst, off(jj));
+    stencil<OPS, RPT, 2, X>(T1 + jw * W, win, lay.fs, dv, n - 1 - wb);
+    __syncthreads();
+#pragma unroll
+    for (int jj = 0; jj < RPT; ++jj) {
+      const int j = rowc(jj), pos = j * kModes + ml;
+      Cd pb = ((mm * g.rinv[j]) * (rp[jj] - rm[jj])) - (dv[0][jj] + dv[1][jj]) + kap * ci(fC[pos]);
+      pb = Cd{zero ? 0.0 : pb.x, zero ? 0.0 : pb.y};
+      if (HEATED && m == 0) tT[jj] = herm_pair<OPS>(tT[jj]);
+      if (ok(jj)) {
+        fA[pos] = pb;
+        if (HEATED) fB[pos] = tT[jj];
+      }
+    }
+  }
+  // ---- transposed pressure and temperature sweeps
+  FactorRegs<OPS, NPT, RPT> L1;
+  L1.template load<false, true>(0, a.fp, opm, nlive, n, t);
+  if constexpr (HEATED) L1.template load<false, true>(NPT - 1, a.ft, opm, nlive, n, t);
+  sweep_dir_t<true, OPS, NPT, RPT>(U1, fld, lay.fs, S, lay.kc_pt, E, n, t);
+  sweep_dir_t<false, OPS, NPT, RPT>(L1, fld, lay.fs, S, lay.kc_pt, E, n, t);
+  // ---- gbar and the temperature masked; fbar+- = rbar+- + (D1^T gbar +
+  // (1 +- m) gbar / r) / 2, fbar_z = rbar_z - i kappa gbar
+  Cd fz[RPT];
+#pragma unroll
+  for (int jj = 0; jj < RPT; ++jj) {
+    const int j = rowc(jj), pos = j * kModes + ml;
+    const bool keep = inner(j) && !zero;
+    if (ok(jj)) fA[pos] = Cd{keep ? fA[pos].x : 0.0, keep ? fA[pos].y : 0.0};
+    if constexpr (HEATED) tT[jj] = Cd{inner(j) ? fB[pos].x : 0.0, inner(j) ? fB[pos].y : 0.0};
+  }
+  __syncthreads();
+  {
+    Cd dg[1][RPT];
+    stencil<OPS, RPT, 1, X>(T1 + jw * W, win, lay.fs, dg, n - 1 - wb);
+#pragma unroll
+    for (int jj = 0; jj < RPT; ++jj) {
+      const int j = rowc(jj), pos = j * kModes + ml;
+      const double ri = g.rinv[j];
+      const Cd gv = fA[pos];
+      rp[jj] = rp[jj] + 0.5 * (dg[0][jj] + ((1.0 + mm) * ri) * gv);
+      rm[jj] = rm[jj] + 0.5 * (dg[0][jj] + ((1.0 - mm) * ri) * gv);
+      fz[jj] = fC[pos] - kap * ci(gv);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int jj = 0; jj < RPT; ++jj)
+    if (ok(jj)) {
+      const int pos = (j0 + jj) * kModes + ml;
+      fA[pos] = rp[jj];
+      fB[pos] = rm[jj];
+      fC[pos] = fz[jj];
+    }
+  fill_weights_t<RPT>(T1, g.lw, n, t);
+  __syncthreads();
+  // ---- input adjoints: Xbar^n = fbar/dt + (1-c) L^T fbar, Nbar^q = c fbar,
+  // Nbar^n = (1-c) fbar, back to (r, theta, z, T)
+  auto put = [&](double2 *p, int jj, Cd v, int bit) {
+    if (!(live && ok(jj))) return;
+    if (!(a.overwrite & bit)) v = ldc(p, off(jj)) + v;
+    stc(p, off(jj), v);
+  };
+  auto put_n = [&](int f, int jj, Cd v) {
+    if (a.nbq) {
+      put(a.nbn + f * fst, jj, ce * v, 2);
+      put(a.nbq + f * fst, jj, a.cc * v, 4);
+    } else if (live && ok(jj)) {  // N^n and N^q are the same array
+      double2 *p = a.nbn + f * fst;
+      const Cd old = a.overwrite & 2 ? Cd{0.0, 0.0} : ldc(p, off(jj));
+      stc(p, off(jj), (old + ce * v) + a.cc * v);
+    }
+  };
+  {
+    Cd l[2][RPT];
+    stencil<OPS, RPT, 2, X>(T1 + jw * W, win, lay.fs, l, n - 1 - wb);
+    const double qp = mm + 1.0, qm = m >= 1 ? mm - 1.0 : 1.0;
+#pragma unroll
+    for (int jj = 0; jj < RPT; ++jj) {
+      const double ri = g.rinv[rowc(jj)], r2 = ri * ri;
+      const Cd x0 = a.idt * rp[jj] + ce * (l[0][jj] - (qp * qp * r2 + k2) * rp[jj]);
+      const Cd x1 = a.idt * rm[jj] + ce * (l[1][jj] - (qm * qm * r2 + k2) * rm[jj]);
+      // X+- = X_r +- i X_theta => Xbar_r = Xbar+ + Xbar-, Xbar_theta = -i (Xbar+ - Xbar-)
+      const Cd dx = x0 - x1, df = rp[jj] - rm[jj];
+      put(a.ubn, jj, x0 + x1, 1);
+      put(a.ubn + fst, jj, Cd{dx.y, -dx.x}, 1);
+      put_n(0, jj, rp[jj] + rm[jj]);
+      put_n(1, jj, Cd{df.y, -df.x});
+    }
+  }
+  {
+    Cd l[1][RPT];
+    stencil<OPS, RPT, 1, X>(T1 + jw * W, win + 2 * lay.fs, lay.fs, l, n - 1 - wb);
+#pragma unroll
+    for (int jj = 0; jj < RPT; ++jj) {
+      const double ri = g.rinv[rowc(jj)], r2 = ri * ri;
+      put(a.ubn + 2 * fst, jj, a.idt * fz[jj] + ce * (l[0][jj] - (mm * mm * r2 + k2) * fz[jj]), 1);
+      put_n(2, jj, fz[jj]);
+    }
+  }
+  if constexpr (HEATED) {
+    __syncthreads();
+#pragma unroll
+    for (int jj = 0; jj < RPT; ++jj)
+      if (ok(jj)) fA[(j0 + jj) * kModes + ml] = tT[jj];
+    __syncthreads();
+    Cd l[1][RPT];
+    stencil<OPS, RPT, 1, X>(T1 + jw * W, win, lay.fs, l, n - 1 - wb);
+#pragma unroll
+    for (int jj = 0; jj < RPT; ++jj) {
+      const double ri = g.rinv[rowc(jj)], r2 = ri * ri;
+      put(a.ubn + 3 * fst, jj,
+          a.idt * tT[jj] + (ce / d.pr) * (l[0][jj] - (mm * mm * r2 + k2) * tT[jj]), 1);
+      put_n(3, jj, tT[jj]);
+    }
+  }
+}
+
 // Launch shape: |k| values per workgroup, rows per thread, LDS layout (within
 // half a compute unit's LDS where the grid fits, so that two workgroups share
 // one).
@@ -738,16 +1217,35 @@ struct StageShape {
 };
 
 template <int OPS>
-StageShape shape_for(const nsc_ctx *c) {
+StageShape shape_for(const nsc_ctx *c, bool adjoint) {
   const int groups = kStageThreads / (2 * OPS), n = c->d.nr;
   const int rpt = (n + groups - 1) / groups, npt = c->d.heated ? 2 : 1;
-  StageShape sh{OPS, rpt, stage_lds<OPS>(n, rpt, npt, c->lds_cu / 2 / 8)};
-  return sh;
+  return StageShape{OPS, rpt, stage_lds<OPS>(n, rpt, npt, adjoint ? win_extra_t(rpt) : 8, !adjoint, c->lds_cu / 2 / 8)};
 }
 
-StageShape stage_shape(const nsc_ctx *c) {
+// Eight |k| per workgroup (whole 128-byte lines of sixteen modes, half the
+// workgroups) once that leaves a workgroup per compute unit, as long as two
+// such workgroups fit one; four otherwise, also for the adjoint at 17 and 18
+// points, where a pair of rows has every row of the column in its transposed
+// windows.
+StageShape stage_shape(const nsc_ctx *c, bool adjoint) {
+  const int n = c->d.nr;
   const long tiles = (long)c->d.mt * ((c->d.kmax + 8) / 8);
-  return c->d.nr <= 64 && tiles >= c->cu_count ? shape_for<8>(c) : shape_for<4>(c);
+  return n <= 64 && !(adjoint && (n == 17 || n == 18)) && tiles >= c->cu_count ? shape_for<8>(c, adjoint) : shape_for<4>(c, adjoint);
+}
+
+// f(ops, rows) with the shape's |k| count and rows per thread as constants
+template <class F>
+hipError_t with_shape(const StageShape &sh, F f) {
+  auto rows = [&](auto ops) {
+    switch (sh.rpt) {
+      case 1: return f(ops, std::integral_constant<int, 1>{});
+      case 2: return f(ops, std::integral_constant<int, 2>{});
+      case 3: return f(ops, std::integral_constant<int, 3>{});
+      default: return f(ops, std::integral_constant<int, 4>{});
+    }
+  };
+  return sh.ops == 8 ? rows(std::integral_constant<int, 8>{}) : rows(std::integral_constant<int, 4>{});
 }
 
 }  // namespace
@@ -755,11 +1253,14 @@ StageShape stage_shape(const nsc_ctx *c) {
 bool stage_fused(const nsc_ctx *c) {
   const Dims &d = c->d;
   if (d.nr > kStageRows) return false;
-  // 32-bit byte offsets: fields, factor rows (72 bytes per operator and
-  // row), responses
-  const size_t nops = (size_t)(d.mt + 1) * (d.kmax + 1);
-  if ((size_t)d.nr * d.nmodes * 16 >> 32 || (size_t)d.nr * nops * 72 >> 32) return false;
-  return (size_t)stage_shape(c).lds.total * sizeof(double) <= (size_t)c->lds_max;
+  // 32-bit byte offsets of the fields and responses (always within reach up
+  // to 64 radial points: the transform lengths bound the modes to 3.8 million)
+  if ((size_t)d.nr * d.nmodes * 16 >> 32) return false;
+  return (size_t)stage_shape(c, false).lds.total * sizeof(double) <= (size_t)c->lds_max;
+}
+
+bool stage_adj_fused(const nsc_ctx *c) {
+  return stage_fused(c) && (size_t)stage_shape(c, true).lds.total * sizeof(double) <= (size_t)c->lds_max;
 }
 
 hipError_t launch_stage(const nsc_ctx *c, const double *u, const double *nn, const double *nq,
@@ -770,9 +1271,9 @@ hipError_t launch_stage(const nsc_ctx *c, const double *u, const double *nn, con
               reinterpret_cast<const double2 *>(nn ? nq : u), reinterpret_cast<double2 *>(out),
               reinterpret_cast<double2 *>(pout), 1.0 / dt, cc, nn ? cc : 0.0, nn ? 1.0 - cc : 0.0,
               walls, pout && nn ? 1 : 0};
-  const StageShape sh = stage_shape(c);
+  const StageShape sh = stage_shape(c, false);
   const int kt = (d.kmax + sh.ops) / sh.ops;
-  auto go = [&](auto ops, auto rows) {
+  return with_shape(sh, [&](auto ops, auto rows) {
     constexpr int OPS = decltype(ops)::value, RPT = decltype(rows)::value;
     auto kern = d.pipe ? (pout ? k_stage<OPS, RPT, false, true, true> : k_stage<OPS, RPT, false, true, false>)
               : d.heated ? (pout ? k_stage<OPS, RPT, true, false, true> : k_stage<OPS, RPT, true, false, false>)
@@ -780,16 +1281,24 @@ hipError_t launch_stage(const nsc_ctx *c, const double *u, const double *nn, con
     hipLaunchKernelGGL(kern, dim3(d.mt * kt), dim3(kStageThreads),
                        (size_t)sh.lds.total * sizeof(double), c->stream, d, c->g, a, sh.lds);
     return hipGetLastError();
-  };
-  auto rows = [&](auto ops) {
-    switch (sh.rpt) {
-      case 1: return go(ops, std::integral_constant<int, 1>{});
-      case 2: return go(ops, std::integral_constant<int, 2>{});
-      case 3: return go(ops, std::integral_constant<int, 3>{});
-      default: return go(ops, std::integral_constant<int, 4>{});
-    }
-  };
-  return sh.ops == 8 ? rows(std::integral_constant<int, 8>{}) : rows(std::integral_constant<int, 4>{});
+  });
+}
+
+hipError_t launch_stage_adj(const nsc_ctx *c, const double *ubar_out, double *ubar_n, double *nbar_n,
+                            double *nbar_q, double dt, double cc, int overwrite) {
+  const Dims &d = c->d;
+  StageAdjArgs a{c->fp, c->fv, c->ft, c->inf, reinterpret_cast<const double2 *>(ubar_out),
+                 reinterpret_cast<double2 *>(ubar_n), reinterpret_cast<double2 *>(nbar_n),
+                 reinterpret_cast<double2 *>(nbar_q), 1.0 / dt, cc, overwrite};
+  const StageShape sh = stage_shape(c, true);
+  const int kt = (d.kmax + sh.ops) / sh.ops;
+  return with_shape(sh, [&](auto ops, auto rows) {
+    constexpr int OPS = decltype(ops)::value, RPT = decltype(rows)::value;
+    auto kern = d.heated ? k_stage_adj<OPS, RPT, true> : k_stage_adj<OPS, RPT, false>;
+    hipLaunchKernelGGL(kern, dim3(d.mt * kt), dim3(kStageThreads),
+                       (size_t)sh.lds.total * sizeof(double), c->stream, d, c->g, a, sh.lds);
+    return hipGetLastError();
+  });
 }
 
 }  // namespace nsc

@@ -172,22 +172,11 @@ int alloc_factors(Factors *f, int nq, int kp1, int nr, bool packed) {
   return NSC_OK;
 }
 
-// The packed columns of a family with packed rows (the adjoint's transposed
-// sweeps), zero where a column entry falls outside the matrix.
-int alloc_columns(Factors *f, int nr) {
-  if (!f->pk) return NSC_OK;
-  const size_t bytes = (size_t)nr * 8 * f->nops * sizeof(double);
-  TRY(dmalloc((void **)&f->pc, bytes));
-  HIPCHK(hipMemset(f->pc, 0, bytes));
-  return NSC_OK;
-}
-
 void free_factors(Factors *f) {
   if (f->vals) (void)hipFree(f->vals);
   if (f->edge) (void)hipFree(f->edge);
   if (f->pk) (void)hipFree(f->pk);
-  if (f->pc) (void)hipFree(f->pc);
-  f->vals = f->edge = f->pk = f->pc = nullptr;
+  f->vals = f->edge = f->pk = nullptr;
 }
 
 int ensure_factors(nsc_ctx *c, double dt, double cc) {
@@ -310,21 +299,18 @@ int nsc::step_vjp_impl(nsc_ctx *c, const double *u, const double *stages,
   const int nc = c->n_corr;
   double *abar = work, *bbar = abar + fld, *xa = bbar + fld, *xb = xa + fld;
   TRY(ensure_factors(c, c->dt, c->c));
-  // the first solve VJP writes ubar and abar, every one writes bbar; only
-  // the nonlinear VJP's output starts from zero
+  // the first solve VJP writes ubar and abar, every one writes bbar
   const double *xbar = ubar_next;
   for (int q = nc; q >= 1; --q) {
     // X^(q+1) = S(u, a, N(X^(q)))
     HIPCHK(launch_solve_vjp(c, xbar, ubar, abar, bbar, c->dt, c->c, q == nc ? 7 : 4));
     double *xn = (xbar == xa) ? xb : xa;
-    HIPCHK(launch_fill_zero(c, xn, fld));
-    HIPCHK(launch_nonlinear_vjp(c, c->precision, stages + (size_t)(q - 1) * fld, bbar, xn));
+    HIPCHK(launch_nonlinear_vjp(c, c->precision, stages + (size_t)(q - 1) * fld, bbar, xn, 1));
     xbar = xn;
   }
-  // X^(1) = S(u, a, a)
-  HIPCHK(launch_solve_vjp(c, xbar, ubar, abar, bbar, c->dt, c->c, nc >= 1 ? 4 : 7));
-  HIPCHK(launch_add(c, abar, bbar, fld));
-  HIPCHK(launch_nonlinear_vjp(c, c->precision, u, abar, ubar));
+  // X^(1) = S(u, a, a): both nonlinear inputs' adjoints into abar
+  HIPCHK(launch_solve_vjp(c, xbar, ubar, abar, nullptr, c->dt, c->c, nc >= 1 ? 0 : 7, bbar));
+  HIPCHK(launch_nonlinear_vjp(c, c->precision, u, abar, ubar, 0));
   return NSC_OK;
 }
 
@@ -352,7 +338,7 @@ int nsc_destroy(nsc_ctx *c) {
   void *ptrs[] = {c->tables, c->tw64_t, c->tw64_z, c->tw32_t, c->tw32_z, c->zbuf, c->wbuf,
                   c->cfl_part, c->cfl_val, c->e_part, c->s_f, c->s_g, c->s_p, c->s_x,
                   c->s_lam, c->s_vjp, c->s_u1, c->s_nn, c->s_nq, c->s_adj, c->s_mean, c->inf.resp, c->inf.ainv,
-                  c->t_row, c->t_cnt, c->t_wt};
+                  c->t_row, c->t_cnt, c->t_wt, c->t_wd};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
   free_factors(&c->fv);
@@ -525,26 +511,29 @@ static int init_impl(nsc_ctx *c, double eta, double Re_i, double Re_o, double Ra
   HIPCHK(hipMemcpy(p_lw, lw.data(), np * nw * sizeof(double), hipMemcpyHostToDevice));
   HIPCHK(hipMemcpy(p_s, s.data(), n * sizeof(int), hipMemcpyHostToDevice));
   c->g = Grid{p_r, p_rinv, p_d1, p_d2, p_s, p_dr, p_cc, p_lw, pipe ? nw : 0};
-  // the adjoint's transposed rows of D2 + D1/r: column j collects the rows
+  // the adjoint's transposed rows of D2 + D1/r and of D1: column j collects the rows
   // whose windows hold it (nine inside, up to thirteen where the one-sided
   // wall windows overlap)
   {
     std::vector<int> trow((size_t)n * kTrans, 0), tcnt(n, 0);
-    std::vector<double> twt((size_t)n * kTrans, 0.0);
+    std::vector<double> twt((size_t)n * kTrans, 0.0), twd((size_t)n * kTrans, 0.0);
     for (int i = 0; i < n; ++i)
       for (int t = 0; t < kStencil; ++t) {
         const int j = s[i] + t;
         if (tcnt[j] >= kTrans) return NSC_ERR_ARG;
         trow[(size_t)j * kTrans + tcnt[j]] = i;
         twt[(size_t)j * kTrans + tcnt[j]] = lw[(size_t)i * kStencil + t];
+        twd[(size_t)j * kTrans + tcnt[j]] = d1[(size_t)i * kStencil + t];
         ++tcnt[j];
       }
     TRY(dmalloc((void **)&c->t_row, trow.size() * sizeof(int)));
     TRY(dmalloc((void **)&c->t_cnt, tcnt.size() * sizeof(int)));
     TRY(dmalloc((void **)&c->t_wt, twt.size() * sizeof(double)));
+    TRY(dmalloc((void **)&c->t_wd, twd.size() * sizeof(double)));
     HIPCHK(hipMemcpy(c->t_row, trow.data(), trow.size() * sizeof(int), hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(c->t_cnt, tcnt.data(), tcnt.size() * sizeof(int), hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(c->t_wt, twt.data(), twt.size() * sizeof(double), hipMemcpyHostToDevice));
+    HIPCHK(hipMemcpy(c->t_wd, twd.data(), twd.size() * sizeof(double), hipMemcpyHostToDevice));
   }
 
   // twiddles
@@ -599,20 +588,15 @@ static int init_impl(nsc_ctx *c, double eta, double Re_i, double Re_o, double Ra
 
   // factors
   const int kp1 = d.kmax + 1;
-  const bool columns = sweeps_unrolled(d, (d.mt + 1) * kp1);
   c->fused = stage_fused(c) ? 1 : 0;
-  const bool packed = c->fused || columns;
+  c->fused_adj = stage_adj_fused(c) ? 1 : 0;
+  const bool packed = c->fused != 0;
   TRY(alloc_factors(&c->fv, d.mt + 1, kp1, n, packed));
   TRY(alloc_factors(&c->fp, d.mt, kp1, n, packed));
   if (d.heated) TRY(alloc_factors(&c->ft, d.mt, kp1, n, packed));
   c->inf.nops = d.mt * kp1;
   TRY(dmalloc((void **)&c->inf.resp, (size_t)8 * n * c->inf.nops * sizeof(double)));
   TRY(dmalloc((void **)&c->inf.ainv, (size_t)4 * c->inf.nops * sizeof(double)));
-  if (columns) {
-    TRY(alloc_columns(&c->fv, n));
-    TRY(alloc_columns(&c->fp, n));
-    if (d.heated) TRY(alloc_columns(&c->ft, n));
-  }
 
   // Delta t-independent pressure factors (slot (0,0): the mean pressure head)
   HIPCHK(launch_factor(c, &c->fp, OP_POISSON, 0.0, 0.0));
@@ -750,7 +734,7 @@ int nsc_nonlinear_vjp(nsc_ctx *c, const double *u, const double *nbar, double *u
   if ((const void *)ubar == (const void *)u || (const void *)ubar == (const void *)nbar)
     return NSC_ERR_ARG;
   if (!theta_fits(c, c->precision, 1)) return NSC_ERR_STATE;
-  HIPCHK(launch_nonlinear_vjp(c, c->precision, u, nbar, ubar));
+  HIPCHK(launch_nonlinear_vjp(c, c->precision, u, nbar, ubar, 0));
   return NSC_OK;
 }
 

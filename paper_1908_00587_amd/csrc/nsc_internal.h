@@ -61,28 +61,17 @@ __host__ __device__ __forceinline__ int odd_off(const Grid &g, int q) { return (
 
 // Compact no-pivot LU factors of a family of radial operators.
 // vals: [N_r][kSlots][nops], edge: [kEdge][nops]; op = q * (K+1) + |k|.
-// pk and pc (only where the fully unrolled sweeps run, else null): the band
-// entries packed per operator, so that a lane fetches four of them with two
-// 16-byte loads.  pk: [N_r][2][nops][4], the L row (slots 0-3) and the U row
-// (slots 5-8) of row j; pc: [N_r][2][nops][4], the L column below the
-// diagonal (L(j+t, j), t = 1..4) and the U column above it (U(j-t, j)),
-// zero outside the matrix (the transposed sweeps of the adjoint).
+// pk (only where the one-kernel implicit stage runs, else null): the band
+// entries packed per operator, [N_r][2][nops][4], the L row (slots 0-3) and
+// the U row (slots 5-8) of row j, so that the four of a row are one 32-byte
+// piece.
 struct Factors {
   double *vals = nullptr;
   double *edge = nullptr;
   double *pk = nullptr;
-  double *pc = nullptr;
   int nq = 0;   // number of q values
   int nops = 0;
 };
-
-// The sweeps run fully unrolled (column in LDS, 32 or 64 radial points,
-// factor offsets within 32 bits) for these grids; nops_max is the largest
-// operator count of the context's factor families.  Their factors carry pk.
-inline bool sweeps_unrolled(const Dims &d, int nops_max) {
-  return (d.nr == 64 || d.nr == 32) &&
-         (size_t)d.nr * kSlots * sizeof(double) * (size_t)nops_max < ((size_t)1 << 31);
-}
 
 // Homogeneous (influence) responses per (m, |k|), op = m*(K+1)+|k|:
 // resp: [4][N_r][nops] pairs (response to data at r_i, at r_o) of p, X+, X-,
@@ -110,6 +99,7 @@ struct nsc_ctx {
   int lds_max = 64 * 1024;  // dynamic LDS bytes per workgroup (device limit)
   int cu_count = 256;       // compute units
   int fused = 0;            // the implicit stage runs as one kernel
+  int fused_adj = 0;        // so does its vector--Jacobian product
   int rows_first = 0;       // stencil kernels walk rows first (long radial rows)
   int lds_cu = 160 * 1024;  // LDS bytes per compute unit
   // host copies
@@ -139,7 +129,7 @@ struct nsc_ctx {
   // transposed rows of D2 + D1/r (cylinders): column j's entries (row,
   // weight), kTrans slots per column, t_cnt[j] of them used
   int *t_row = nullptr, *t_cnt = nullptr;
-  double *t_wt = nullptr;
+  double *t_wt = nullptr, *t_wd = nullptr;  // (t_wd: the same for D1)
   double *s_vjp = nullptr;  // adjoint workspaces of nsc_step_vjp: 4 states (allocated on first use)
   double *s_u1 = nullptr;   // [F][N_r][modes] complex intermediate state
   double *s_nn = nullptr;   // [F][N_r][modes] complex N^n
@@ -203,7 +193,6 @@ hipError_t launch_influence_pressure(const nsc_ctx *c);
 hipError_t launch_influence_setup(const nsc_ctx *c);
 hipError_t launch_rhs(const nsc_ctx *c, const double *u, const double *nn,
                       const double *nq, double dt, double cc);
-hipError_t launch_fill_zero(const nsc_ctx *c, double *p, size_t n);
 hipError_t launch_add(const nsc_ctx *c, double *y, const double *x, size_t n);
 hipError_t launch_solve_sweeps(const nsc_ctx *c, int stage, const double *nn, const double *nq,
                                double cc, int walls, int want_p);
@@ -218,13 +207,18 @@ hipError_t launch_finalize(const nsc_ctx *c, double *out, double *p_out);
 hipError_t launch_energy(const nsc_ctx *c, const double *u, double *e_dev);
 hipError_t launch_seed(const nsc_ctx *c, const double *amps, double *out_pert);
 hipError_t launch_add_base(const nsc_ctx *c, const double *pert_tilde, double *out);
-// overwrite: bit 1 ubar_n, 2 nbar_n, 4 nbar_q written instead of accumulated
+// overwrite: bit 1 ubar_n, 2 nbar_n, 4 nbar_q written instead of accumulated;
+// nbar_q null: N^n and N^q are one array, whose adjoint goes to nbar_n
+// (scratch: a state for the kernel sequence, which forms them apart)
 hipError_t launch_solve_vjp(const nsc_ctx *c, const double *ubar_out, double *ubar_n,
                             double *nbar_n, double *nbar_q, double dt, double cc,
-                            int overwrite = 0);
+                            int overwrite = 0, double *scratch = nullptr);
+bool stage_adj_fused(const nsc_ctx *c);
+hipError_t launch_stage_adj(const nsc_ctx *c, const double *ubar_out, double *ubar_n, double *nbar_n,
+                            double *nbar_q, double dt, double cc, int overwrite);
 hipError_t launch_energy_grad(const nsc_ctx *c, const double *u, double *gout);
 hipError_t launch_nonlinear_vjp(const nsc_ctx *c, int prec, const double *u, const double *nbar,
-                                double *ubar);
+                                double *ubar, int overwrite);
 
 // The step VJP (nsc_step_vjp): argument checks, and its sequence with the
 // four state-sized adjoint workspaces at `work`.
