@@ -75,121 +75,180 @@ struct OpRow {
   }
 };
 
-constexpr int kBW = 17;  // band window width: columns i-8 .. i+8
-constexpr int kFacThreads = 32;
-
-// One thread per operator: op = q*(K+1) + |k|.  Band elimination without
-// pivoting over a sliding 9-row window held in LDS.  blockIdx.y picks one of
+// LU factors of every operator, one lane per operator (op = q*(K+1) + |k|),
+// row by row: row i subtracts the L_ik-fold of the finished U rows k of its
+// window, whose fill stays inside it (no pivoting).  blockIdx.y picks one of
 // two operator sets of the same kind and shift (velocity and temperature
 // Helmholtz operators differ only in beta): both factorise in one launch.
+//
+// Rows 8 .. N-5 only need the last four U rows, kept in registers and turned
+// over by unrolling four rows; their weights are loaded four rows ahead.  The
+// first eight and last four rows read the U rows (up to eight entries there)
+// from LDS, where each lane keeps its last eight.  One wavefront per compute
+// unit is what the smaller grids have, so the time is one wavefront's
+// instruction stream, and past about 16000 operators the factors' writes.
+// Before (elimination of a nine-row window in LDS, the band entries also
+// stored one array per entry) -> now: 32 x 16 x 16 operators' rows 58 -> 22 us,
+// 64 x 64 x 64 twice (heated) 99 -> 29, 128 x 256 x 256 610 -> 145.
+constexpr int kFacThreads = 64;
+constexpr int kFacRow = 10;  // LDS doubles per U row: U_{i,i+1..i+8}, 1/U_ii, pad
+
 __global__ void __launch_bounds__(kFacThreads)
-k_factor(Dims d, Grid g, Factors F0, Factors F1, int kind, double alpha, double beta0,
-         double beta1, int q_off) {
-  __shared__ double win[9 * kBW * kFacThreads];
+k_factor(Dims d, Grid g, Factors F0, Factors F1, int kind, double alpha, double beta0, double beta1) {
+  __shared__ __align__(16) double ring[8 * kFacThreads * kFacRow];
   const Factors F = blockIdx.y == 0 ? F0 : F1;
   const double beta = blockIdx.y == 0 ? beta0 : beta1;
   const int tid = threadIdx.x;
   const int op = blockIdx.x * kFacThreads + tid;
   if (op >= F.nops) return;
-  auto W = [&](int ring, int bi) -> double & { return win[(ring * kBW + bi) * kFacThreads + tid]; };
   const int n = d.nr;
   const int kp1 = d.kmax + 1;
-  const int q = op / kp1 + q_off;
-  const int ka = op - (op / kp1) * kp1;
+  const int q = op / kp1;
+  const int ka = op - q * kp1;
   const double kap = (double)ka * d.kz;
   OpRow R{kind, alpha, beta, (double)q * (double)q, kap * kap, d.pipe, odd_off(g, q)};
   const size_t nops = F.nops;
   // the pure-Neumann Poisson operator of (q = 0, kappa = 0) is singular and
   // never used; its slot holds the mean pressure-head operator instead
   if (kind == OP_POISSON && q == 0 && ka == 0) R.kind = OP_MEAN_PRESSURE;
-  auto store_row = [&](int i, const double *a, int s) {
-    const int ring = i % 9;
-    for (int bi = 0; bi < kBW; ++bi) W(ring, bi) = 0.0;
-    for (int t = 0; t < kStencil; ++t) W(ring, s + t - i + 8) = a[t];
+  auto slot = [&](int i) { return reinterpret_cast<Dbl2 *>(ring + ((i & 7) * kFacThreads + tid) * kFacRow); };
+  // row i to memory: L_{i,i-4..i-1}, U_{i,i+1..i+4} and 1/U_ii
+  auto store = [&](int i, const double (&lo)[4], const double (&up)[4], double dinv) {
+    Dbl2 *o = reinterpret_cast<Dbl2 *>(F.pk + ((size_t)i * 2 * nops + op) * 4);
+    o[0] = Dbl2{lo[0], lo[1]};
+    o[1] = Dbl2{lo[2], lo[3]};
+    o += 2 * nops;
+    o[0] = Dbl2{up[0], up[1]};
+    o[1] = Dbl2{up[2], up[3]};
+    F.di[(size_t)i * nops + op] = dinv;
   };
-  const int first = n < 9 ? n : 9;
-  for (int i = 0; i < first; ++i) {
+  // a row by the ring, with its diagonal at entry D of its window
+  auto ring_row = [&](auto diag, int i) {
+    constexpr int D = decltype(diag)::value;
     double a[kStencil];
     int s;
     R.row(g, n, i, a, s);
-    store_row(i, a, s);
-  }
-  // Elimination of column k from the B rows below the pivot over the B
-  // columns to its right: every operand is read before any result is
-  // written (the rows are distinct ring slots), so the reads issue together.
-  auto eliminate = [&](auto bsz, int rk, double dinv) {
-    constexpr int B = decltype(bsz)::value;
-    double pk[B], lv[B], rw[B][B];
 #pragma unroll
-    for (int t = 0; t < B; ++t) pk[t] = W(rk, 9 + t);
+    for (int t = 0; t < D; ++t) {
+      const Dbl2 *u = slot(i - D + t);
+      const Dbl2 u01 = u[0], u23 = u[1], u45 = u[2], u67 = u[3];
+      const double uk[8] = {u01.x, u01.y, u23.x, u23.y, u45.x, u45.y, u67.x, u67.y};
+      a[t] *= u[4].x;
 #pragma unroll
-    for (int r = 1; r <= B; ++r) {
-      const int ri = rk + r < 9 ? rk + r : rk + r - 9;
-      lv[r - 1] = W(ri, 8 - r);
-#pragma unroll
-      for (int t = 1; t <= B; ++t) rw[r - 1][t - 1] = W(ri, 8 - r + t);
+      for (int c = t + 1; c < kStencil; ++c) a[c] -= a[t] * uk[c - t - 1];
     }
+    const double dinv = 1.0 / a[D];
+    double lo[4], uk[8];
 #pragma unroll
-    for (int r = 1; r <= B; ++r) {
-      const int ri = rk + r < 9 ? rk + r : rk + r - 9;
-      const double l = lv[r - 1] * dinv;
-      W(ri, 8 - r) = l;
+    for (int t = 0; t < 4; ++t) lo[t] = D - 4 + t >= 0 ? a[D - 4 + t < 0 ? 0 : D - 4 + t] : 0.0;
 #pragma unroll
-      for (int t = 1; t <= B; ++t) W(ri, 8 - r + t) = rw[r - 1][t - 1] - l * pk[t - 1];
-    }
+    for (int t = 0; t < 8; ++t) uk[t] = D + 1 + t < kStencil ? a[D + 1 + t < kStencil ? D + 1 + t : 0] : 0.0;
+    const double up[4] = {uk[0], uk[1], uk[2], uk[3]};
+    store(i, lo, up, dinv);
+    Dbl2 *u = slot(i);
+    u[0] = Dbl2{uk[0], uk[1]};
+    u[1] = Dbl2{uk[2], uk[3]};
+    u[2] = Dbl2{uk[4], uk[5]};
+    u[3] = Dbl2{uk[6], uk[7]};
+    u[4] = Dbl2{dinv, 0.0};
+    // entries past the band: U of rows 0..3, L of rows N-4..N-1
+#pragma unroll
+    for (int c = D + 5; c < kStencil; ++c)
+      F.edge[(size_t)(edge_off(D) + c - (D + 5)) * nops + op] = a[c];
+#pragma unroll
+    for (int c = 0; c <= D - 5; ++c)
+      F.edge[(size_t)(10 + edge_off(8 - D) + c) * nops + op] = a[c];
   };
-  for (int k = 0; k < n; ++k) {
-    // the row entering the window at the end of this step: its table reads
-    // are issued first and consumed last
-    double anx[kStencil];
-    int snx = 0;
-    const bool more = k + 9 < n;
-    if (more) R.row(g, n, k + 9, anx, snx);
-    const int rk = k % 9;
-    const double dinv = 1.0 / W(rk, 8);
-    // Rows k+5.. have no entry in column k and row k none right of k+4 when
-    // the 9-point windows of rows k-4..k+8 are all centred; near the walls
-    // the one-sided windows reach 8 rows and columns.  Columns past N-1 hold
-    // zeros in every live row; ring slots of rows past N-1 hold rows already
-    // written out, whose updates are never read.
-    if (k >= 4 && more)
-      eliminate(std::integral_constant<int, 4>{}, rk, dinv);
-    else
-      eliminate(std::integral_constant<int, 8>{}, rk, dinv);
-    // row k is final
-    double lo[4], up[4];
-    for (int t = 1; t <= 4; ++t) {
-      const int c = k - t;
-      lo[4 - t] = c >= 0 ? W(rk, c - k + 8) : 0.0;
-      const int cu = k + t;
-      up[t - 1] = cu < n ? W(rk, cu - k + 8) : 0.0;
+  ring_row(std::integral_constant<int, 0>{}, 0);
+  ring_row(std::integral_constant<int, 1>{}, 1);
+  ring_row(std::integral_constant<int, 2>{}, 2);
+  ring_row(std::integral_constant<int, 3>{}, 3);
+  int i = 4;
+  for (; i < 8 && i < n - 4; ++i) ring_row(std::integral_constant<int, 4>{}, i);
+  if (i + 4 <= n - 4) {
+    // rows i .. i+3, the U rows of i-4 .. i-1 in registers
+    double uk[4][4], dv[4], w[4][kStencil], ri[4];
+    auto weights = [&](int r, int j) {
+      const double *p = g.lw + R.off + (j < n ? j : n - 1) * kStencil;
+#pragma unroll
+      for (int t = 0; t < kStencil; ++t) w[r][t] = p[t];
+      ri[r] = g.rinv[j < n ? j : n - 1];
+    };
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const Dbl2 *u = slot(4 + r);
+      const Dbl2 u01 = u[0], u23 = u[1];
+      uk[r][0] = u01.x;
+      uk[r][1] = u01.y;
+      uk[r][2] = u23.x;
+      uk[r][3] = u23.y;
+      dv[r] = u[4].x;
+      weights(r, i + r);
     }
-    double *v = F.vals + (size_t)k * kSlots * nops + op;
-    for (int t = 0; t < 4; ++t) {
-      v[(size_t)t * nops] = lo[t];
-      v[(size_t)(5 + t) * nops] = up[t];
-    }
-    v[(size_t)4 * nops] = dinv;
-    if (F.pk) {
-      auto at = [&](double *base, int row, int part) {
-        return base + (((size_t)row * 2 + part) * nops + op) * 4;
-      };
-      for (int t = 0; t < 4; ++t) {
-        at(F.pk, k, 0)[t] = lo[t];
-        at(F.pk, k, 1)[t] = up[t];
+    const double f = kind == OP_HELMHOLTZ ? -beta : 1.0;
+    for (; i + 4 <= n - 4; i += 4) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        double a[kStencil];
+#pragma unroll
+        for (int t = 0; t < kStencil; ++t) a[t] = f * w[r][t];
+        const double sh = R.q2 * ri[r] * ri[r] + R.k2;
+        a[4] = kind == OP_HELMHOLTZ ? a[4] + (alpha + beta * sh) : a[4] - sh;
+        weights(r, i + r + 4);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const int k = (r + t) & 3;  // U row i + r - 4 + t
+          a[t] *= dv[k];
+#pragma unroll
+          for (int c = 0; c < 4; ++c) a[t + 1 + c] -= a[t] * uk[k][c];
+        }
+        const double dinv = 1.0 / a[4];
+        const double lo[4] = {a[0], a[1], a[2], a[3]};
+        dv[r] = dinv;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) uk[r][c] = a[5 + c];
+        store(i + r, lo, uk[r], dinv);
+        if (i >= n - 16) {  // within reach of the last rows
+          Dbl2 *u = slot(i + r);
+          u[0] = Dbl2{uk[r][0], uk[r][1]};
+          u[1] = Dbl2{uk[r][2], uk[r][3]};
+          u[2] = u[3] = Dbl2{0.0, 0.0};
+          u[4] = Dbl2{dinv, 0.0};
+        }
       }
     }
-    if (k <= 3)
-      for (int c = k + 5; c <= 8 && c < n; ++c)
-        F.edge[(size_t)(edge_off(k) + c - (k + 5)) * nops + op] = W(rk, c - k + 8);
-    if (k >= n - 4) {
-      const int t = n - 1 - k;
-      for (int c = n - 9; c <= k - 5; ++c)
-        if (c >= 0) F.edge[(size_t)(10 + edge_off(t) + c - (n - 9)) * nops + op] = W(rk, c - k + 8);
-    }
-    if (more) store_row(k + 9, anx, snx);
   }
+  for (; i < n - 4; ++i) ring_row(std::integral_constant<int, 4>{}, i);
+  ring_row(std::integral_constant<int, 5>{}, n - 4);
+  ring_row(std::integral_constant<int, 6>{}, n - 3);
+  ring_row(std::integral_constant<int, 7>{}, n - 2);
+  ring_row(std::integral_constant<int, 8>{}, n - 1);
 }
+
+// Rows of the packed factors of one operator.
+struct RowL {
+  double l4, l3, l2, l1;  // L_{j,j-4..j-1}
+};
+struct RowU {
+  double u1, u2, u3, u4;  // U_{j,j+1..j+4}
+};
+struct RowsOf {
+  const double *pk, *di;
+  size_t nops;
+  __device__ __forceinline__ RowsOf(const Factors &F, int op)
+      : pk(F.pk + (size_t)op * 4), di(F.di + op), nops(F.nops) {}
+  __device__ __forceinline__ RowL l(int j) const {
+    const Dbl2 *p = reinterpret_cast<const Dbl2 *>(pk + (size_t)j * 8 * nops);
+    const Dbl2 a = p[0], b = p[1];
+    return {a.x, a.y, b.x, b.y};
+  }
+  __device__ __forceinline__ RowU u(int j) const {
+    const Dbl2 *p = reinterpret_cast<const Dbl2 *>(pk + ((size_t)j * 2 + 1) * 4 * nops);
+    const Dbl2 a = p[0], b = p[1];
+    return {a.x, a.y, b.x, b.y};
+  }
+  __device__ __forceinline__ double dinv(int j) const { return di[(size_t)j * nops]; }
+};
 
 // Forward/back substitution for one lane.  RHS(j) gives b_j, COL(j) the
 // storage of y_j then x_j (LDS or global, read back by the same lane).  The
@@ -198,69 +257,108 @@ k_factor(Dims d, Grid g, Factors F0, Factors F1, int kind, double alpha, double 
 // compiler can schedule them ahead of the recurrence; only the one-sided
 // wall rows (U to column 8 in rows 0..3, L from column N-9 in rows N-4..N-1)
 // take the extra edge terms, in peeled loops.
-template <typename V, typename RHS, typename COL>
+// The factor rows are loaded AHEAD rows before their use.
+template <typename V, int AHEAD = 4, typename RHS, typename COL>
 __device__ __forceinline__ void lu_solve(const Factors &F, int op, int n, RHS rhs, COL col) {
   const size_t nops = F.nops;
-  const double *__restrict__ vals = F.vals + op;
+  const RowsOf R(F, op);
   const double *__restrict__ edge = F.edge + op;
-  V y1{}, y2{}, y3{}, y4{};
-#pragma unroll 4
-  for (int j = 0; j < n - 4; ++j) {
-    const double *v = vals + (size_t)j * kSlots * nops;
-    const double l4 = v[0], l3 = v[nops], l2 = v[2 * nops], l1 = v[3 * nops];
-    V y = rhs(j);
-    y = y - l1 * y1;
-    y = y - l2 * y2;
-    y = y - l3 * y3;
-    y = y - l4 * y4;
-    y4 = y3;
-    y3 = y2;
-    y2 = y1;
-    y1 = y;
-    col(j) = y;
+  {
+    V y1{}, y2{}, y3{}, y4{};
+    RowL v[AHEAD];
+#pragma unroll
+    for (int r = 0; r < AHEAD; ++r) v[r] = R.l(r < n ? r : n - 1);
+    auto row = [&](const RowL &l, int j) {
+      V y = rhs(j);
+      y = y - l.l1 * y1;
+      y = y - l.l2 * y2;
+      y = y - l.l3 * y3;
+      y = y - l.l4 * y4;
+      y4 = y3;
+      y3 = y2;
+      y2 = y1;
+      y1 = y;
+      col(j) = y;
+    };
+    int j = 0;
+    for (; j + AHEAD <= n - 4; j += AHEAD) {
+#pragma unroll
+      for (int r = 0; r < AHEAD; ++r) {
+        const RowL l = v[r];
+        v[r] = R.l(j + AHEAD + r < n ? j + AHEAD + r : n - 1);
+        row(l, j + r);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < AHEAD; ++r)
+      if (j + r < n - 4) row(v[r], j + r);
   }
 #pragma unroll
-  for (int j = n - 4; j < n; ++j) {
-    const double *v = vals + (size_t)j * kSlots * nops;
+  for (int tt = 3; tt >= 0; --tt) {
+    const int j = n - 1 - tt;
+    const RowL v = R.l(j);
     V y = rhs(j);
+    y = y - v.l1 * col(j - 1);
+    y = y - v.l2 * col(j - 2);
+    y = y - v.l3 * col(j - 3);
+    y = y - v.l4 * col(j - 4);
 #pragma unroll
-    for (int t = 1; t <= 4; ++t) y = y - v[(size_t)(4 - t) * nops] * col(j - t);
-    const int tt = n - 1 - j;
-#pragma unroll
-    for (int c = n - 9; c <= j - 5; ++c) y = y - edge[(size_t)(10 + edge_off(tt) + c - (n - 9)) * nops] * col(c);
+    for (int c = 0; c <= 3 - tt; ++c) y = y - edge[(size_t)(10 + edge_off(tt) + c) * nops] * col(n - 9 + c);
     col(j) = y;
   }
-  V x1{}, x2{}, x3{}, x4{};
-#pragma unroll 4
-  for (int j = n - 1; j >= 4; --j) {
-    const double *v = vals + (size_t)j * kSlots * nops;
-    const double di = v[4 * nops], u1 = v[5 * nops], u2 = v[6 * nops], u3 = v[7 * nops], u4 = v[8 * nops];
-    V x = col(j);
-    x = x - u1 * x1;
-    x = x - u2 * x2;
-    x = x - u3 * x3;
-    x = x - u4 * x4;
-    x = di * x;
-    x4 = x3;
-    x3 = x2;
-    x2 = x1;
-    x1 = x;
-    col(j) = x;
+  {
+    V x1{}, x2{}, x3{}, x4{};
+    RowU v[AHEAD];
+    double di[AHEAD];
+#pragma unroll
+    for (int r = 0; r < AHEAD; ++r) {
+      const int a = n - 1 - r > 0 ? n - 1 - r : 0;
+      v[r] = R.u(a);
+      di[r] = R.dinv(a);
+    }
+    auto row = [&](const RowU &u, double d, int j) {
+      V x = col(j);
+      x = x - u.u1 * x1;
+      x = x - u.u2 * x2;
+      x = x - u.u3 * x3;
+      x = x - u.u4 * x4;
+      x = d * x;
+      x4 = x3;
+      x3 = x2;
+      x2 = x1;
+      x1 = x;
+      col(j) = x;
+    };
+    int j = n - 1;
+    for (; j - AHEAD >= 3; j -= AHEAD) {
+#pragma unroll
+      for (int r = 0; r < AHEAD; ++r) {
+        const RowU u = v[r];
+        const double d = di[r];
+        const int a = j - AHEAD - r > 0 ? j - AHEAD - r : 0;
+        v[r] = R.u(a);
+        di[r] = R.dinv(a);
+        row(u, d, j - r);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < AHEAD; ++r)
+      if (j - r >= 4) row(v[r], di[r], j - r);
   }
 #pragma unroll
   for (int j = 3; j >= 0; --j) {
-    const double *v = vals + (size_t)j * kSlots * nops;
+    const RowU v = R.u(j);
     V x = col(j);
-#pragma unroll
-    for (int t = 1; t <= 4; ++t) x = x - v[(size_t)(4 + t) * nops] * col(j + t);
+    x = x - v.u1 * col(j + 1);
+    x = x - v.u2 * col(j + 2);
+    x = x - v.u3 * col(j + 3);
+    x = x - v.u4 * col(j + 4);
 #pragma unroll
     for (int c = j + 5; c <= 8; ++c) x = x - edge[(size_t)(edge_off(j) + c - (j + 5)) * nops] * col(c);
-    col(j) = v[(size_t)4 * nops] * x;
+    col(j) = R.dinv(j) * x;
   }
 }
 
-// The two responses (Neumann data at r_i, at r_o) of one operator: solved
-// together, so that a lane reads each factor row once for both.
 __device__ __forceinline__ Cd d1_row(const Grid &g, int j, const Cd *x, size_t stride, int off = 0) {
   const int s = g.s[j];
   const double *w = g.d1 + off + j * kStencil;
@@ -271,9 +369,11 @@ __device__ __forceinline__ Cd d1_row(const Grid &g, int j, const Cd *x, size_t s
 }
 
 // Homogeneous responses and inverse influence matrices per (m, |k|), in
-// three passes: the pressure responses p_j (Neumann data e_0, e_{N-1}; do not
+// two parts: the pressure responses p_j (Neumann data e_0, e_{N-1}; do not
 // depend on the step size, computed once), then the six velocity responses
-// (X+, X-, h for each p_j) in parallel, then the 2x2 influence matrices.
+// (X+, X-, h for each p_j) and the 2x2 influence matrices.  The two responses
+// of an operator are solved together, as the parts of a complex number, so that
+// a lane reads each factor row once for both.
 __global__ void __launch_bounds__(64) k_influence_p(Dims d, Factors fp, Influence I) {
   const int op = blockIdx.x * blockDim.x + threadIdx.x;
   if (op >= I.nops) return;
@@ -291,79 +391,39 @@ __global__ void __launch_bounds__(64) k_influence_p(Dims d, Factors fp, Influenc
                [&](int j) -> Cd & { return P[(size_t)j * ns]; });
 }
 
-constexpr int kInfLanes = 32;  // operators per workgroup with the columns in LDS
-
-template <bool USE_LDS>
-__global__ void __launch_bounds__(64) k_influence_x(Dims d, Grid g, Factors fv, Influence I) {
-  extern __shared__ Cd inf_lds[];  // USE_LDS: [2][N_r][lanes] pressure and solution columns
-  const int lanes = blockDim.x;
-  const int op = blockIdx.x * lanes + threadIdx.x;
-  const int kind = blockIdx.y;  // 0: X+, 1: X-, 2: h
-  if (op >= I.nops) return;
-  const int n = d.nr;
-  const int kp1 = d.kmax + 1;
-  const int m = op / kp1;
-  const int ka = op - m * kp1;
-  const size_t ns = I.nops;
-  Cd *resp = reinterpret_cast<Cd *>(I.resp) + op;
-  Cd *out = resp + (size_t)(1 + kind) * n * ns;
-  if (m == 0 && ka == 0) {
-    for (int j = 0; j < n; ++j) out[(size_t)j * ns] = Cd{0.0, 0.0};
-    return;
-  }
-  const double mm = (double)m;
-  const int q = kind == 0 ? m + 1 : (kind == 1 ? (m >= 1 ? m - 1 : 1 - m) : m);
-  // X+ = H_{m+1}^-1 (-(D1 p - m p / r)), X- = H_{|m-1|}^-1 (-(D1 p + m p / r)),
-  // h = H_m^-1 p so that X_z = -i kappa h
-  auto rhs = [&](int j, const Cd *p, size_t stride) {
-    if ((j == 0 && !d.pipe) || j == n - 1) return Cd{0.0, 0.0};
-    const Cd pj = p[(size_t)j * stride];
-    if (kind == 2) return pj;
-    const Cd dp = d1_row(g, j, p, stride, odd_off(g, m));  // p of order m
-    const Cd mp = (mm * g.rinv[j]) * pj;
-    return kind == 0 ? Cd{0.0, 0.0} - (dp - mp) : Cd{0.0, 0.0} - (dp + mp);
-  };
-  if constexpr (USE_LDS) {
-    // each lane owns one pressure column and one solution column in LDS (no
-    // sharing, so no barrier): the back substitution and the stencil reads
-    // stay on chip
-    Cd *pl = inf_lds + threadIdx.x;
-    Cd *xl = inf_lds + (size_t)n * lanes + threadIdx.x;
-#pragma unroll 8
-    for (int j = 0; j < n; ++j) pl[j * lanes] = resp[(size_t)j * ns];
-    lu_solve<Cd>(fv, q * kp1 + ka, n, [&](int j) { return rhs(j, pl, lanes); },
-                 [&](int j) -> Cd & { return xl[j * lanes]; });
-#pragma unroll 8
-    for (int j = 0; j < n; ++j) out[(size_t)j * ns] = xl[j * lanes];
-  } else {
-    lu_solve<Cd>(fv, q * kp1 + ka, n, [&](int j) { return rhs(j, resp, ns); },
-                 [&](int j) -> Cd & { return out[(size_t)j * ns]; });
-  }
+// Right sides of the velocity responses of pressure p:
+// X+ = H_{m+1}^-1 (-(D1 p - m p / r)), X- = H_{|m-1|}^-1 (-(D1 p + m p / r)),
+// h = H_m^-1 p so that X_z = -i kappa h (kind 0, 1, 2)
+__device__ __forceinline__ Cd response_rhs(const Dims &d, const Grid &g, int kind, int m, int j, const Cd *p,
+                                           size_t stride) {
+  if ((j == 0 && !d.pipe) || j == d.nr - 1) return Cd{0.0, 0.0};
+  const Cd pj = p[(size_t)j * stride];
+  if (kind == 2) return pj;
+  const Cd dp = d1_row(g, j, p, stride, odd_off(g, m));  // p of order m
+  const Cd mp = ((double)m * g.rinv[j]) * pj;
+  return kind == 0 ? Cd{0.0, 0.0} - (dp - mp) : Cd{0.0, 0.0} - (dp + mp);
+}
+// Azimuthal order of a response's operator
+__device__ __forceinline__ int response_q(int kind, int m) {
+  return kind == 0 ? m + 1 : (kind == 1 ? (m >= 1 ? m - 1 : 1 - m) : m);
 }
 
-__global__ void __launch_bounds__(64) k_influence_a(Dims d, Grid g, Influence I) {
-  const int op = blockIdx.x * blockDim.x + threadIdx.x;
-  if (op >= I.nops) return;
-  const int n = d.nr;
-  const int kp1 = d.kmax + 1;
-  const int m = op / kp1;
-  const int ka = op - m * kp1;
+// Inverse influence matrix of one operator from its responses' columns
+// (rows strided by `stride`).
+__device__ __forceinline__ void influence_matrix(const Dims &d, const Grid &g, const Influence &I, int op, int m,
+                                                 const Cd *Xp, const Cd *Xm, size_t stride) {
   const size_t ns = I.nops;
-  if (m == 0 && ka == 0) {
-    for (int e = 0; e < 4; ++e) I.ainv[(size_t)e * ns + op] = 0.0;
-    return;
-  }
+  const int n = d.nr;
   const double mm = (double)m;
   // A[w][jj] = wall divergence of response jj (walls carry zero velocity)
   double A[2][2];
   const int off = odd_off(g, m + 1);  // X+- of orders m +- 1
-  const Cd *Xp = reinterpret_cast<const Cd *>(I.resp) + (size_t)n * ns + op;
-  const Cd *Xm = Xp + (size_t)n * ns;
+#pragma unroll
   for (int w = 0; w < 2; ++w) {
     const int j = w == 0 ? 0 : n - 1;
     const double ri = g.rinv[j];
-    const Cd v = 0.5 * ((d1_row(g, j, Xp, ns, off) + ((1.0 + mm) * ri) * Xp[(size_t)j * ns]) +
-                        (d1_row(g, j, Xm, ns, off) + ((1.0 - mm) * ri) * Xm[(size_t)j * ns]));
+    const Cd v = 0.5 * ((d1_row(g, j, Xp, stride, off) + ((1.0 + mm) * ri) * Xp[(size_t)j * stride]) +
+                        (d1_row(g, j, Xm, stride, off) + ((1.0 - mm) * ri) * Xm[(size_t)j * stride]));
     A[w][0] = v.x;
     A[w][1] = v.y;
   }
@@ -374,10 +434,86 @@ __global__ void __launch_bounds__(64) k_influence_a(Dims d, Grid g, Influence I)
     A[0][1] = 0.0;
   }
   const double det = A[0][0] * A[1][1] - A[0][1] * A[1][0];
-  I.ainv[0 * ns + op] = A[1][1] / det;
-  I.ainv[1 * ns + op] = -A[0][1] / det;
-  I.ainv[2 * ns + op] = -A[1][0] / det;
-  I.ainv[3 * ns + op] = A[0][0] / det;
+  const bool mean = m == 0 && op == 0;  // (0, 0) has no influence matrix
+  I.ainv[0 * ns + op] = mean ? 0.0 : A[1][1] / det;
+  I.ainv[1 * ns + op] = mean ? 0.0 : -A[0][1] / det;
+  I.ainv[2 * ns + op] = mean ? 0.0 : -A[1][0] / det;
+  I.ainv[3 * ns + op] = mean ? 0.0 : A[0][0] / det;
+}
+
+// Velocity responses and influence matrices of sixteen operators per
+// workgroup.  All threads load the pressure columns and form the right sides
+// in LDS; three wavefronts then solve one kind each in place, one lane per
+// operator, the factor rows loaded eight ahead; all threads write the columns out.
+// What bounds it is the serial sweep of a lane.
+// Before (one lane per operator and kind with its own LDS columns, the matrices
+// in a second kernel) -> now: 32 x 16 x 16 31 -> 16 us, 64 x 64 x 64 51 -> 22;
+// 128 x 256 x 256 720 -> 730 (one workgroup per compute unit). With eight
+// operators per workgroup: 15, 34 and 839 us.
+constexpr int kInfOps = 16;
+constexpr int kInfThreads = 256;
+
+__global__ void __launch_bounds__(kInfThreads) k_influence_v(Dims d, Grid g, Factors fv, Influence I) {
+  extern __shared__ __align__(16) Cd inf_lds[];  // [p, X+, X-, h][N_r][kInfOps]
+  constexpr int groups = kInfThreads / kInfOps;
+  const int t = threadIdx.x, o = t % kInfOps;
+  const int op = blockIdx.x * kInfOps + o;
+  const bool live = op < I.nops;
+  const int n = d.nr;
+  const int kp1 = d.kmax + 1;
+  const int opc = live ? op : I.nops - 1;
+  const int m = opc / kp1;
+  const int ka = opc - m * kp1;
+  const size_t ns = I.nops;
+  Cd *resp = reinterpret_cast<Cd *>(I.resp) + opc;
+  Cd *col = inf_lds + o;
+  const size_t fs = (size_t)n * kInfOps;  // between the columns of one kind and the next
+#pragma unroll 4
+  for (int j = t / kInfOps; j < n; j += groups) col[j * kInfOps] = resp[(size_t)j * ns];
+  __syncthreads();
+  for (int j = t / kInfOps; j < n; j += groups)
+#pragma unroll
+    for (int kind = 0; kind < 3; ++kind)
+      col[(1 + kind) * fs + j * kInfOps] = response_rhs(d, g, kind, m, j, col, kInfOps);
+  __syncthreads();
+  const int kind = t / 64;
+  if (kind < 3 && t % 64 < kInfOps) {
+    Cd *x = col + (1 + kind) * fs;
+    lu_solve<Cd, 8>(fv, response_q(kind, m) * kp1 + ka, n, [&](int j) { return x[j * kInfOps]; },
+                     [&](int j) -> Cd & { return x[j * kInfOps]; });
+  }
+  __syncthreads();
+  if (!live) return;
+  // (0, 0): no pressure response, zero columns
+#pragma unroll
+  for (int kd = 0; kd < 3; ++kd)
+    for (int j = t / kInfOps; j < n; j += groups)
+      resp[((size_t)(1 + kd) * n + j) * ns] = col[(1 + kd) * fs + j * kInfOps];
+  if (t < kInfOps) influence_matrix(d, g, I, op, m, col + fs, col + 2 * fs, kInfOps);
+}
+
+// The same in two kernels, columns in global memory, for columns past the LDS.
+__global__ void __launch_bounds__(64) k_influence_x(Dims d, Grid g, Factors fv, Influence I) {
+  const int op = blockIdx.x * blockDim.x + threadIdx.x;
+  const int kind = blockIdx.y;
+  if (op >= I.nops) return;
+  const int n = d.nr;
+  const int kp1 = d.kmax + 1;
+  const int m = op / kp1;
+  const int ka = op - m * kp1;
+  const size_t ns = I.nops;
+  const Cd *p = reinterpret_cast<const Cd *>(I.resp) + op;
+  Cd *out = reinterpret_cast<Cd *>(I.resp) + op + (size_t)(1 + kind) * n * ns;
+  lu_solve<Cd>(fv, response_q(kind, m) * kp1 + ka, n, [&](int j) { return response_rhs(d, g, kind, m, j, p, ns); },
+               [&](int j) -> Cd & { return out[(size_t)j * ns]; });
+}
+
+__global__ void __launch_bounds__(64) k_influence_a(Dims d, Grid g, Influence I) {
+  const int op = blockIdx.x * blockDim.x + threadIdx.x;
+  if (op >= I.nops) return;
+  const size_t ns = I.nops;
+  const Cd *Xp = reinterpret_cast<const Cd *>(I.resp) + (size_t)d.nr * ns + op;
+  influence_matrix(d, g, I, op, op / (d.kmax + 1), Xp, Xp + (size_t)d.nr * ns, ns);
 }
 
 // Nine-point stencil sums over R consecutive rows j0 .. j0+nrow-1 of NF
@@ -987,27 +1123,34 @@ __global__ void k_add_base(Dims d, Grid g, const double2 *__restrict__ pert, dou
 template <typename V, typename RHS, typename COL>
 __device__ __forceinline__ void lu_solve_t(const Factors &F, int op, int n, RHS rhs, COL col) {
   const size_t nops = F.nops;
-  const double *__restrict__ vals = F.vals + op;
+  const RowsOf R(F, op);
   const double *__restrict__ edge = F.edge + op;
-  auto Vv = [&](int row, int slot) { return vals[((size_t)row * kSlots + slot) * nops]; };
+  auto Lv = [&](int row, int c) { return R.pk[(size_t)row * 8 * nops + c]; };
+  auto Uv = [&](int row, int c) { return R.pk[((size_t)row * 2 + 1) * 4 * nops + c]; };
   for (int j = 0; j < 9; ++j) {
     V y = rhs(j);
     for (int t = 1; t <= 4; ++t)
-      if (j - t >= 0) y = y - Vv(j - t, 4 + t) * col(j - t);
+      if (j - t >= 0) y = y - Uv(j - t, t - 1) * col(j - t);
     for (int c = 0; c <= 3; ++c)
       if (j - c >= 5) y = y - edge[(size_t)(edge_off(c) + j - c - 5) * nops] * col(c);
-    col(j) = Vv(j, 4) * y;
+    col(j) = R.dinv(j) * y;
   }
+  // the last four U rows (then L rows) stay in registers
+  RowU r1 = R.u(8), r2 = R.u(7), r3 = R.u(6), r4 = R.u(5);
   V y1 = col(8), y2 = col(7), y3 = col(6), y4 = col(5);
 #pragma unroll 4
   for (int j = 9; j < n; ++j) {
-    const double a1 = Vv(j - 1, 5), a2 = Vv(j - 2, 6), a3 = Vv(j - 3, 7), a4 = Vv(j - 4, 8), di = Vv(j, 4);
+    const RowU r0 = R.u(j);
     V y = rhs(j);
-    y = y - a1 * y1;
-    y = y - a2 * y2;
-    y = y - a3 * y3;
-    y = y - a4 * y4;
-    y = di * y;
+    y = y - r1.u1 * y1;
+    y = y - r2.u2 * y2;
+    y = y - r3.u3 * y3;
+    y = y - r4.u4 * y4;
+    y = R.dinv(j) * y;
+    r4 = r3;
+    r3 = r2;
+    r2 = r1;
+    r1 = r0;
     y4 = y3;
     y3 = y2;
     y2 = y1;
@@ -1017,20 +1160,25 @@ __device__ __forceinline__ void lu_solve_t(const Factors &F, int op, int n, RHS 
   for (int j = n - 1; j >= n - 9; --j) {
     V x = col(j);
     for (int t = 1; t <= 4; ++t)
-      if (j + t < n) x = x - Vv(j + t, 4 - t) * col(j + t);
+      if (j + t < n) x = x - Lv(j + t, 4 - t) * col(j + t);
     for (int c = n - 4; c <= n - 1; ++c)
       if (c - j >= 5) x = x - edge[(size_t)(10 + edge_off(n - 1 - c) + j - (n - 9)) * nops] * col(c);
     col(j) = x;
   }
+  RowL q1 = R.l(n - 9), q2 = R.l(n - 8), q3 = R.l(n - 7), q4 = R.l(n - 6);
   V x1 = col(n - 9), x2 = col(n - 8), x3 = col(n - 7), x4 = col(n - 6);
 #pragma unroll 4
   for (int j = n - 10; j >= 0; --j) {
-    const double a1 = Vv(j + 1, 3), a2 = Vv(j + 2, 2), a3 = Vv(j + 3, 1), a4 = Vv(j + 4, 0);
+    const RowL q0 = R.l(j);
     V x = col(j);
-    x = x - a1 * x1;
-    x = x - a2 * x2;
-    x = x - a3 * x3;
-    x = x - a4 * x4;
+    x = x - q1.l1 * x1;
+    x = x - q2.l2 * x2;
+    x = x - q3.l3 * x3;
+    x = x - q4.l4 * x4;
+    q4 = q3;
+    q3 = q2;
+    q2 = q1;
+    q1 = q0;
     x4 = x3;
     x3 = x2;
     x2 = x1;
@@ -1399,7 +1547,7 @@ inline dim3 mode_grid(const nsc_ctx *c, int y, int z = 1) {
 
 hipError_t launch_factor(const nsc_ctx *c, Factors *f, int kind, double alpha, double beta) {
   hipLaunchKernelGGL(k_factor, dim3((f->nops + kFacThreads - 1) / kFacThreads), dim3(kFacThreads), 0,
-                     c->stream, c->d, c->g, *f, *f, kind, alpha, beta, beta, 0);
+                     c->stream, c->d, c->g, *f, *f, kind, alpha, beta, beta);
   return hipGetLastError();
 }
 
@@ -1408,7 +1556,7 @@ hipError_t launch_factor2(const nsc_ctx *c, Factors *f0, Factors *f1, int kind, 
   const int nmax = f0->nops > f1->nops ? f0->nops : f1->nops;
   hipLaunchKernelGGL(k_factor, dim3((nmax + kFacThreads - 1) / kFacThreads, 2),
                      dim3(kFacThreads), 0, c->stream, c->d, c->g, *f0, *f1, kind, alpha, beta0,
-                     beta1, 0);
+                     beta1);
   return hipGetLastError();
 }
 
@@ -1419,18 +1567,14 @@ hipError_t launch_influence_pressure(const nsc_ctx *c) {
 }
 
 hipError_t launch_influence_setup(const nsc_ctx *c) {
-  const dim3 gx((c->inf.nops + kInfLanes - 1) / kInfLanes, 3);
-  // LDS columns only while every workgroup is resident at once: the solves
-  // are latency chains, and at larger sizes the LDS would cap the waves in
-  // flight below what the global-memory variant keeps
-  const size_t shm = (size_t)2 * c->d.nr * kInfLanes * sizeof(Cd);
-  const size_t resident = shm <= (size_t)c->lds_max ? (size_t)c->cu_count * (c->lds_cu / shm) : 0;
-  if ((size_t)gx.x * gx.y <= resident)
-    hipLaunchKernelGGL(k_influence_x<true>, gx, dim3(kInfLanes), shm, c->stream, c->d, c->g, c->fv,
-                       c->inf);
-  else
-    hipLaunchKernelGGL(k_influence_x<false>, dim3((c->inf.nops + 63) / 64, 3), dim3(64), 0,
+  const size_t shm = (size_t)4 * c->d.nr * kInfOps * sizeof(Cd);
+  if (shm <= (size_t)c->lds_max) {
+    hipLaunchKernelGGL(k_influence_v, dim3((c->inf.nops + kInfOps - 1) / kInfOps), dim3(kInfThreads), shm,
                        c->stream, c->d, c->g, c->fv, c->inf);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(k_influence_x, dim3((c->inf.nops + 63) / 64, 3), dim3(64), 0, c->stream, c->d, c->g,
+                     c->fv, c->inf);
   hipLaunchKernelGGL(k_influence_a, dim3((c->inf.nops + 63) / 64), dim3(64), 0, c->stream, c->d,
                      c->g, c->inf);
   return hipGetLastError();

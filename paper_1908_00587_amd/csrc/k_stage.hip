@@ -42,9 +42,6 @@ constexpr int kBlock = 12;          // rows per unrolled block of a recurrence
 constexpr int kRing = 6;            // factor rows in registers (kBlock is a multiple)
 constexpr int kPad = 8;             // complex values between fields: next field on the other banks
 
-// (a native vector: arrays of HIP's double2 class do not stay in registers)
-typedef double Dbl2 __attribute__((ext_vector_type(2)));
-
 // 16 or 8 bytes at a uniform base plus a 32-bit byte offset (one scalar pair
 // and one vector register per address; stage_fused keeps the arrays below
 // 4 GiB)
@@ -214,9 +211,9 @@ struct FactorRegs {
 #pragma unroll
       for (int i = 0; i < DQ; ++i) {
         const int r0 = first_row<DOWN>(i, RD, n);
-        const double *p = F.vals + ((size_t)r0 * kSlots + 4) * F.nops + op0;
+        const double *p = F.di + (size_t)r0 * F.nops + op0;
         dg[s][i] = at<double>(p, (unsigned)(lane_row<DOWN>(t / OPS + i * RD, n) - r0) *
-                                     ((unsigned)F.nops * (8 * kSlots)) + col);
+                                     ((unsigned)F.nops * 8) + col);
       }
     }
   }

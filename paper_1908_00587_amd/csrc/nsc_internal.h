@@ -12,7 +12,6 @@ namespace nsc {
 
 constexpr int kStencil = 9;    // nine-point radial stencils (section 2.1 default)
 constexpr int kHalf = 4;       // stencil half width
-constexpr int kSlots = 9;      // compact LU row: L[4] | 1/U_jj | U[4]
 constexpr int kTrans = 16;     // slots per column of a transposed stencil (13 used at most)
 constexpr int kEdge = 20;      // extra U entries of rows 0..3 + extra L of rows N-4..N-1
 constexpr int kMaxRadix = 8;
@@ -60,15 +59,14 @@ struct Dims {
 __host__ __device__ __forceinline__ int odd_off(const Grid &g, int q) { return (q & 1) ? g.podd : 0; }
 
 // Compact no-pivot LU factors of a family of radial operators.
-// vals: [N_r][kSlots][nops], edge: [kEdge][nops]; op = q * (K+1) + |k|.
-// pk (only where the one-kernel implicit stage runs, else null): the band
-// entries packed per operator, [N_r][2][nops][4], the L row (slots 0-3) and
-// the U row (slots 5-8) of row j, so that the four of a row are one 32-byte
-// piece.
+// op = q * (K+1) + |k|.  pk: the band entries, [N_r][2][nops][4], the L row
+// (columns j-4..j-1) and the U row (j+1..j+4) of row j, so that the four of a
+// row are one 32-byte piece; di: [N_r][nops] the inverse diagonal 1/U_jj;
+// edge: [kEdge][nops] the entries past the band.
 struct Factors {
-  double *vals = nullptr;
-  double *edge = nullptr;
   double *pk = nullptr;
+  double *di = nullptr;
+  double *edge = nullptr;
   int nq = 0;   // number of q values
   int nops = 0;
 };

@@ -9,6 +9,10 @@ namespace nsc {
 // left of it in rows N-1-t).
 __device__ __forceinline__ int edge_off(int t) { return t * 4 - (t * (t - 1)) / 2; }
 
+// 16-byte load and store unit; arrays of it stay in registers (arrays of
+// HIP's double2 do not)
+typedef double Dbl2 __attribute__((ext_vector_type(2)));
+
 struct Cd {
   double x, y;
 };
