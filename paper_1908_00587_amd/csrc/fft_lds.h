@@ -499,7 +499,21 @@ constexpr int ct_wave_lines(int n) {
   return gl;
 }
 
-template <typename T, bool INV, int N, int S>
+// Lines per wavefront of the z passes (workgroups of kZLines lines): four,
+// two, one, the most that keep a lane to about nine values.  More values cost
+// registers (or scratch) and with them wavefronts, fewer leave lanes idle.
+// Both passes of 64 rows, 4 / 2 / 1 lines: FP64 96 points 30.0 / 32 / 41 us,
+// 192 points 65 / 55 / 73; FP64 384 points (27 rows) - / 115 / 101, FP32 432
+// points (21 rows) - / 108 / 90.
+constexpr int kZLines = 8;
+constexpr int ct_z_lines(int n) {
+  int l = 4;
+  while (l > 1 && (l * n > 600 || l > ct_wave_lines(n))) l /= 2;
+  return l;
+}
+
+// Stages S.. of GL lines of one wavefront, the planner's order.
+template <typename T, bool INV, int N, int GL, int S>
 __device__ __forceinline__ void ct_stages(LdsC2<T> b0, int nl, LdsTw<T> tw, int lane) {
   constexpr CtRadices P = ct_radices(N);
   if constexpr (S < P.nst) {
@@ -507,22 +521,22 @@ __device__ __forceinline__ void ct_stages(LdsC2<T> b0, int nl, LdsTw<T> tw, int 
     constexpr int NS = ct_ns(N, S);
     constexpr int PP = 1 << pad_shift<T>();
     constexpr bool AFF = (N / R) % PP == 0 && (NS % PP == 0 || (NS == 1 && PP % R == 0));
-    stage_body<T, R, INV, ct_wave_regs(N) / R, false, AFF, true>(b0, nl, N, lds_line<T>(N), NS,
-                                                                 tw, lane, 64);
-    ct_stages<T, INV, N, S + 1>(b0, nl, tw, lane);
+    stage_body<T, R, INV, (GL * (N / R) + 63) / 64, false, AFF, true>(b0, nl, N, lds_line<T>(N), NS,
+                                                                      tw, lane, 64);
+    ct_stages<T, INV, N, GL, S + 1>(b0, nl, tw, lane);
   }
 }
 
 // fft_wave for the fixed length N (line stride lds_line<T>(N)).
 template <typename T, bool INV, int N>
 __device__ __forceinline__ void fft_wave_ct(C2<T> *buf, int nlines, const TwT<T> *tw, int lane) {
-  constexpr int GL = ct_wave_lines(N);
-  static_assert(GL > 0, "length too long for a wavefront-scope transform");
+  constexpr int GL = ct_z_lines(N);
+  static_assert(ct_wave_lines(N) > 0, "length too long for a wavefront-scope transform");
   constexpr int LS = lds_line<T>(N);
   LdsTw<T> twl = to_lds_tw<T>(tw);
   for (int l0 = 0; l0 < nlines; l0 += GL) {
     const int nl = nlines - l0 < GL ? nlines - l0 : GL;
-    ct_stages<T, INV, N, 0>(to_lds(buf + l0 * LS), nl, twl, lane);
+    ct_stages<T, INV, N, GL, 0>(to_lds(buf + l0 * LS), nl, twl, lane);
   }
 }
 
@@ -558,7 +572,7 @@ constexpr int ct_ns_ord(int n, int ord, int s) {
 
 // Stages S.. of the order ORD; SKIP: the last stage, if radix 3, stores only
 // its outer two output thirds.
-template <typename T, bool INV, int N, int ORD, int S, bool SKIP>
+template <typename T, bool INV, int N, int ORD, int S, bool SKIP, int GL>
 __device__ __forceinline__ void ct_stages_ord(LdsC2<T> b0, int nl, LdsTw<T> tw, int lane) {
   constexpr CtRadices P = ct_order(N, ORD);
   if constexpr (S < P.nst) {
@@ -567,24 +581,24 @@ __device__ __forceinline__ void ct_stages_ord(LdsC2<T> b0, int nl, LdsTw<T> tw, 
     constexpr int PP = 1 << pad_shift<T>();
     constexpr bool AFF = (N / R) % PP == 0 && (NS % PP == 0 || (NS == 1 && PP % R == 0));
     constexpr bool SKIPMID = SKIP && S == P.nst - 1 && R == 3;
-    stage_body<T, R, INV, ct_wave_regs(N) / R, false, AFF, true, SKIPMID>(
+    stage_body<T, R, INV, (GL * (N / R) + 63) / 64, false, AFF, true, SKIPMID>(
         b0, nl, N, lds_line<T>(N), NS, tw, lane, 64);
-    ct_stages_ord<T, INV, N, ORD, S + 1, SKIP>(b0, nl, tw, lane);
+    ct_stages_ord<T, INV, N, ORD, S + 1, SKIP, GL>(b0, nl, tw, lane);
   }
 }
 
-// Stages S0.. of the order ORD over `nlines` lines of one wavefront (line
-// stride lds_line<T>(N)), in groups of the lines a wavefront carries.
-template <typename T, bool INV, int N, int ORD, int S0, bool SKIP>
+// Stages S0.. of the order ORD over `nlines` <= NL lines of one wavefront
+// (line stride lds_line<T>(N)), in groups of the lines a wavefront carries.
+template <typename T, bool INV, int N, int ORD, int S0, bool SKIP, int NL>
 __device__ __forceinline__ void fft_wave_ct_ord(C2<T> *buf, int nlines, const TwT<T> *tw,
                                                 int lane) {
-  constexpr int GL = ct_wave_lines(N);
+  constexpr int GL = ct_wave_lines(N) < NL ? ct_wave_lines(N) : NL;
   static_assert(GL > 0, "length too long for a wavefront-scope transform");
   constexpr int LS = lds_line<T>(N);
   LdsTw<T> twl = to_lds_tw<T>(tw);
   for (int l0 = 0; l0 < nlines; l0 += GL) {
     const int nl = nlines - l0 < GL ? nlines - l0 : GL;
-    ct_stages_ord<T, INV, N, ORD, S0, SKIP>(to_lds(buf + l0 * LS), nl, twl, lane);
+    ct_stages_ord<T, INV, N, ORD, S0, SKIP, GL>(to_lds(buf + l0 * LS), nl, twl, lane);
   }
 }
 

@@ -141,9 +141,62 @@ __device__ void mean_row(const Dims &d, const Grid &g, const double2 *__restrict
   mean[6 * n + j] = dt;
 }
 
+// Launch bounds of the z passes of length n (0: any): the workgroup's size (a
+// bound of 1024 threads keeps a lane to 128 registers, and the stages of lengths
+// such as 180 and 300 then spill a hundred: 180 points FP64 both passes of 64
+// rows 168 us against 77), and for FP32 lines of one per wavefront, whose LDS
+// leaves room, four wavefronts per SIMD (720 points 172 against 140 us).
+constexpr int z_bound(int n) {
+  return n == 0 || n > 768 ? kFftThreads : 64 * ((kZLines + ct_z_lines(n) - 1) / ct_z_lines(n));
+}
+constexpr int z_waves(int n, int esize) { return n > 0 && esize == 8 && z_bound(n) >= 512 ? 4 : 1; }
+
+// Threads per (r, z) line set and LDS pad of the fixed-length theta kernels.
+// One wavefront runs a set without workgroup barriers, but large sets leave
+// too few wavefronts on a compute unit's LDS: above 18 KB of lines (FP64 384
+// points 196 -> 169 us on 48 x 384 sets; FP32 heated 576 points 153 -> 84 us)
+// or 512 points (FP32 768 points 96 -> 66 us on 24 x 192 sets) four
+// wavefronts share a set; at 13 KB and below one is faster (FP64 192 points
+// 58 against 67 us on 64 x 192 sets, FP32 480 points 69 against 87 us).
+constexpr int fx_group(int n, int esize, int lines) {
+  return n > 768 ? 512 : (n > 512 || lines * lds_line_s<3>(n) * esize > 18 * 1024 ? 256 : 64);
+}
+constexpr int fx_pad(int n) { return n > 768 ? 5 : 3; }
+
+
+// Line sets per workgroup of the fixed-length theta kernels: the number that
+// puts the most sets on a compute unit's LDS (the twiddles are shared), up to
+// 256 threads of one wavefront per set; 0 if one set does not fit.  Where four
+// wavefronts share a set, a larger workgroup has to gain a quarter, as all of
+// it meets at every stage's barriers (FP64 heated 216 points, 8 sets a compute
+// unit in workgroups of four against 7 alone: 158 against 97 us).
+constexpr int fx_sets(int n, int esize, int lines, int lds_max, int lds_cu) {
+  const int G = fx_group(n, esize, lines), pad = fx_pad(n);
+  const int line = (n + (n >> pad) + 1) * esize, tws = n * 16;
+  int best = 0, sets = 0;
+  for (int s = 1; s * G <= (G == 64 ? kThetaWaveThreads : kFftThreads); ++s) {
+    const int shm = tws + s * lines * line;
+    if (shm > lds_max) break;
+    const int per_cu = lds_cu / shm * s;
+    if (G == 64 ? per_cu > best : 4 * per_cu >= 5 * best) {
+      best = per_cu;
+      sets = s;
+    }
+  }
+  return sets;
+}
+// ... and the launch bound that follows on gfx950's 160 KB: as tight as the
+// workgroup, for the registers (a bound of 1024 threads spills in the lines past
+// 480 points)
+constexpr int kLds = 160 * 1024;
+constexpr int fx_bound(int n, int esize, int lines) {
+  const int s = fx_sets(n, esize, lines, kLds, kLds);
+  return (s < 1 ? 1 : s) * fx_group(n, esize, lines);
+}
+
 constexpr int ZU = 4;  // z-pass items per round of loads (2: about half the gain)
 template <typename T, int NF, bool PIPE = false>
-__global__ void __launch_bounds__(kFftThreads) k_zinv(Dims d, Grid g, FftPlan pz, const double2 *__restrict__ u,
+__global__ void __launch_bounds__(z_bound(NF), z_waves(NF, sizeof(C2<T>))) k_zinv(Dims d, Grid g, FftPlan pz, const double2 *__restrict__ u,
                        C2<T> *__restrict__ Z, const TwT<T> *__restrict__ tw, int tm, int drop_mean,
                        double *__restrict__ mean) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -484,7 +537,7 @@ __device__ __forceinline__ void pack_radix3(LdsC2<T> bl, const C2<T> *src, size_
 //     every finite value, so the maximum also flags them), reduced across
 //     each wavefront by DPP.
 template <typename T, int N, int NI, int G, int SH>
-__global__ void __launch_bounds__(G == 64 ? kThetaWaveThreads : kFftThreads)
+__global__ void __launch_bounds__(fx_bound(N, sizeof(C2<T>), (NI + 1) / 2))
 k_theta_fx(Dims d, Grid g, const C2<T> *__restrict__ Z, C2<T> *__restrict__ W,
            const TwT<T> *__restrict__ tw, double dth, double dzs, double *__restrict__ cfl_part,
            int want_cfl, const double *__restrict__ mean) {
@@ -517,7 +570,7 @@ k_theta_fx(Dims d, Grid g, const C2<T> *__restrict__ Z, C2<T> *__restrict__ W,
   pack_radix3<T, MT, NI, G, SH, LS>(bl, zl, fstride, tid);
   if constexpr (WAVE) {
     wave_sync();
-    fft_wave_ct_ord<T, true, N, ORD_3FIRST, 1, false>(buf, NP, tws, tid);
+    fft_wave_ct_ord<T, true, N, ORD_3FIRST, 1, false, NP>(buf, NP, tws, tid);
   } else {
     __syncthreads();
     ct_stages_grp<T, true, N, ORD_3FIRST, 1, false, NP, G, SH>(bl, twl, tid);
@@ -567,7 +620,7 @@ k_theta_fx(Dims d, Grid g, const C2<T> *__restrict__ Z, C2<T> *__restrict__ W,
   }
   if constexpr (WAVE) {
     wave_sync();
-    fft_wave_ct_ord<T, false, N, ORD_3LAST, 0, true>(buf, 2, tws, tid);
+    fft_wave_ct_ord<T, false, N, ORD_3LAST, 0, true, 2>(buf, 2, tws, tid);
   } else {
     __syncthreads();
     ct_stages_grp<T, false, N, ORD_3LAST, 0, true, 2, G, SH>(bl, twl, tid);
@@ -708,7 +761,7 @@ __device__ void cfl_reduce(const double *__restrict__ part, int n, double *out, 
 }
 
 template <typename T, int NF>
-__global__ void __launch_bounds__(kFftThreads) k_zfwd(Dims d, Grid g, FftPlan pz, const C2<T> *__restrict__ W,
+__global__ void __launch_bounds__(z_bound(NF), z_waves(NF, sizeof(C2<T>))) k_zfwd(Dims d, Grid g, FftPlan pz, const C2<T> *__restrict__ W,
                        const double2 *__restrict__ u, double2 *__restrict__ nh,
                        const TwT<T> *__restrict__ tw, int tm, double scale,
                        const double *__restrict__ mean, const double *__restrict__ cfl_part,
@@ -758,7 +811,7 @@ __global__ void __launch_bounds__(kFftThreads) k_zfwd(Dims d, Grid g, FftPlan pz
     const int l0 = wv * per;
     const int cnt = nl - l0 < per ? nl - l0 : per;
     if (cnt > 0)
-      fft_wave_ct_ord<T, false, NF, ORD_3LAST, 0, true>(buf + l0 * ls, cnt, tws,
+      fft_wave_ct_ord<T, false, NF, ORD_3LAST, 0, true, ct_z_lines(NF)>(buf + l0 * ls, cnt, tws,
                                                        (int)(threadIdx.x & 63));
     __syncthreads();
   } else {
@@ -830,7 +883,7 @@ __global__ void __launch_bounds__(kFftThreads) k_zfwd(Dims d, Grid g, FftPlan pz
 
 // Nbar (Hermitian-projected, divided by c_m and N_theta N_z) -> inverse z FFT.
 template <typename T, int NF>
-__global__ void __launch_bounds__(kFftThreads)
+__global__ void __launch_bounds__(z_bound(NF), z_waves(NF, sizeof(C2<T>)))
 k_zinv_adj(Dims d, FftPlan pz, const double2 *__restrict__ nb, C2<T> *__restrict__ W,
            const TwT<T> *__restrict__ tw, int tm, double scale) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -941,7 +994,7 @@ k_theta_adj(Dims d, FftPlan pt, C2<T> *__restrict__ Z, const C2<T> *__restrict__
 // the forward transforms of the input adjoints run radix 3 last and drop the
 // middle third.
 template <typename T, int N, int NI, int G, int SH>
-__global__ void __launch_bounds__(G == 64 ? kThetaWaveThreads : kFftThreads)
+__global__ void __launch_bounds__(fx_bound(N, sizeof(C2<T>), (NI + 1) / 2 + 2))
 k_theta_adj_fx(Dims d, C2<T> *__restrict__ Z, const C2<T> *__restrict__ W,
                const TwT<T> *__restrict__ tw) {
   constexpr int MT = N / 3;
@@ -971,7 +1024,7 @@ k_theta_adj_fx(Dims d, C2<T> *__restrict__ Z, const C2<T> *__restrict__ W,
   pack_radix3<T, MT, HEATED ? 4 : 3, G, SH, LS>(bl + NP * LS, wl, fstride, tid);
   if constexpr (WAVE) {
     wave_sync();
-    fft_wave_ct_ord<T, true, N, ORD_3FIRST, 1, false>(buf, NP + 2, tws, tid);
+    fft_wave_ct_ord<T, true, N, ORD_3FIRST, 1, false, NP + 2>(buf, NP + 2, tws, tid);
   } else {
     __syncthreads();
     ct_stages_grp<T, true, N, ORD_3FIRST, 1, false, NP + 2, G, SH>(bl, twl, tid);
@@ -1006,7 +1059,7 @@ k_theta_adj_fx(Dims d, C2<T> *__restrict__ Z, const C2<T> *__restrict__ W,
   }
   if constexpr (WAVE) {
     wave_sync();
-    fft_wave_ct_ord<T, false, N, ORD_3LAST, 0, true>(buf, NP, tws, tid);
+    fft_wave_ct_ord<T, false, N, ORD_3LAST, 0, true, NP>(buf, NP, tws, tid);
   } else {
     __syncthreads();
     ct_stages_grp<T, false, N, ORD_3LAST, 0, true, NP, G, SH>(bl, twl, tid);
@@ -1028,7 +1081,7 @@ k_theta_adj_fx(Dims d, C2<T> *__restrict__ Z, const C2<T> *__restrict__ W,
 
 // Forward z FFT of the input adjoints, times c_m -> Dbar[n_in][N_r][modes].
 template <typename T, int NF>
-__global__ void __launch_bounds__(kFftThreads)
+__global__ void __launch_bounds__(z_bound(NF), z_waves(NF, sizeof(C2<T>)))
 k_zfwd_adj(Dims d, FftPlan pz, const C2<T> *__restrict__ Z, double2 *__restrict__ db,
            const TwT<T> *__restrict__ tw, int tm) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -1089,7 +1142,7 @@ int z_lines(const nsc_ctx *c, size_t esize) {
   // cache-line boundaries, took 29 % longer in the z-inverse pass; 16-line
   // tiles of 768-point lines, one workgroup per CU, 3 % and 11 % longer in
   // the FP32 z passes)
-  if (tm > 8) tm = 8;
+  if (tm > kZLines) tm = kZLines;
   if (tm > 1) tm = 1 << (31 - __builtin_clz((unsigned)tm));
   if (tm > c->d.mt) tm = c->d.mt;
   if (tm < 1) tm = 1;
@@ -1108,51 +1161,13 @@ int z_threads(const FftPlan &p, int tm) {
   return block_for(p, tm, 256);
 }
 
-// Launch shape of the fixed-length theta kernel: G threads per line set,
-// line pad period 2^SH, and the sets per workgroup that put the most line
-// sets on a compute unit's LDS (up to 1024 threads); sets = 0 if one set
-// does not fit.
+// Launch shape of the fixed-length theta kernel; sets = 0 if one set does not
+// fit the LDS.
 struct FxLaunch {
   int sets;
   dim3 grid;
   size_t shm;
 };
-
-FxLaunch fx_launch(const nsc_ctx *c, size_t esize, int np, int G, int SH) {
-  const int nt = c->d.nt;
-  const size_t line = (size_t)(nt + (nt >> SH) + 1) * esize;
-  const size_t tws = (size_t)nt * 16;
-  FxLaunch L{0, dim3(1), 0};
-  int best = 0;
-  const int maxt = G == 64 ? kThetaWaveThreads : kFftThreads;  // the kernel's launch bound
-  for (int s = 1; s * G <= maxt; ++s) {
-    const size_t shm = tws + (size_t)s * np * line;
-    if (shm > (size_t)c->lds_max) break;
-    const int per_cu = (int)((size_t)c->lds_cu / shm) * s;
-    if (per_cu > best) {
-      best = per_cu;
-      L.sets = s;
-      L.shm = shm;
-    }
-  }
-  if (L.sets > 0) {
-    const int nsets = c->d.nz * c->d.nr;
-    L.grid = dim3((nsets + L.sets - 1) / L.sets);
-  }
-  return L;
-}
-
-// Threads per (r, z) line set and LDS pad of the fixed-length theta kernels.
-// One wavefront runs a set without workgroup barriers, but large sets leave
-// too few wavefronts on a compute unit's LDS: above 18 KB of lines (FP64 384
-// points 196 -> 169 us on 48 x 384 sets; FP32 heated 576 points 153 -> 84 us)
-// or 512 points (FP32 768 points 96 -> 66 us on 24 x 192 sets) four
-// wavefronts share a set; at 13 KB and below one is faster (FP64 192 points
-// 58 against 67 us on 64 x 192 sets, FP32 480 points 69 against 87 us).
-constexpr int fx_group(int n, int esize, int lines) {
-  return n > 768 ? 512 : (n > 512 || lines * lds_line_s<3>(n) * esize > 18 * 1024 ? 256 : 64);
-}
-constexpr int fx_pad(int n) { return n > 768 ? 5 : 3; }
 
 template <typename T>
 const TwT<T> *tw_z(const nsc_ctx *c) {
@@ -1171,11 +1186,12 @@ struct ZLaunch {
   dim3 grid;
   size_t shm;
 };
-template <typename T>
+template <typename T, int NF>
 ZLaunch z_launch(const nsc_ctx *c, int nf) {
   ZLaunch L;
   L.tm = z_lines(c, sizeof(C2<T>));
-  L.threads = z_threads(c->plan_z, L.tm);
+  if constexpr (NF > 0 && NF <= 768) L.threads = 64 * ((L.tm + ct_z_lines(NF) - 1) / ct_z_lines(NF));
+  else L.threads = z_threads(c->plan_z, L.tm);
   L.grid = dim3((c->d.mt + L.tm - 1) / L.tm, c->d.nr, nf);
   L.shm = ((size_t)L.tm * lds_line<T>(c->d.nz) + tw_slots<T>(c->d.nz)) * sizeof(C2<T>);
   return L;
@@ -1186,7 +1202,7 @@ ZLaunch z_launch(const nsc_ctx *c, int nf) {
 template <typename T, int NF>
 struct LenPass {
   static hipError_t zinv(const nsc_ctx *c, const double *u, int drop_mean) {
-    const ZLaunch L = z_launch<T>(c, c->n_in);
+    const ZLaunch L = z_launch<T, NF>(c, c->n_in);
     auto kern = c->d.pipe ? k_zinv<T, NF, true> : k_zinv<T, NF, false>;
     hipLaunchKernelGGL(kern, L.grid, dim3(L.threads), L.shm, c->stream, c->d, c->g, c->plan_z,
                        reinterpret_cast<const double2 *>(u), reinterpret_cast<C2<T> *>(c->zbuf),
@@ -1195,7 +1211,7 @@ struct LenPass {
   }
   static hipError_t zfwd(const nsc_ctx *c, const double *u, double *nh, double *cfl_out,
                          double *cfl_host) {
-    const ZLaunch L = z_launch<T>(c, c->n_out);
+    const ZLaunch L = z_launch<T, NF>(c, c->n_out);
     const double scale = 1.0 / ((double)c->d.nt * (double)c->d.nz);
     hipLaunchKernelGGL((k_zfwd<T, NF>), L.grid, dim3(L.threads), L.shm, c->stream, c->d, c->g,
                        c->plan_z, reinterpret_cast<const C2<T> *>(c->wbuf),
@@ -1205,7 +1221,7 @@ struct LenPass {
     return hipGetLastError();
   }
   static hipError_t zinv_adj(const nsc_ctx *c, const double *nbar) {
-    const ZLaunch L = z_launch<T>(c, c->n_out);
+    const ZLaunch L = z_launch<T, NF>(c, c->n_out);
     const double scale = 1.0 / ((double)c->d.nt * (double)c->d.nz);
     hipLaunchKernelGGL((k_zinv_adj<T, NF>), L.grid, dim3(L.threads), L.shm, c->stream, c->d,
                        c->plan_z, reinterpret_cast<const double2 *>(nbar),
@@ -1213,7 +1229,7 @@ struct LenPass {
     return hipGetLastError();
   }
   static hipError_t zfwd_adj(const nsc_ctx *c) {
-    const ZLaunch L = z_launch<T>(c, c->n_in);
+    const ZLaunch L = z_launch<T, NF>(c, c->n_in);
     hipLaunchKernelGGL((k_zfwd_adj<T, NF>), L.grid, dim3(L.threads), L.shm, c->stream, c->d,
                        c->plan_z, reinterpret_cast<const C2<T> *>(c->zbuf),
                        reinterpret_cast<double2 *>(c->s_adj), tw_z<T>(c), L.tm);
@@ -1223,7 +1239,13 @@ struct LenPass {
   static FxLaunch shape(const nsc_ctx *c, int adjoint) {
     constexpr int es = sizeof(C2<T>);
     const int np = (c->n_in + 1) / 2 + (adjoint ? 2 : 0);
-    return fx_launch(c, es, np, fx_group(NF, es, np), fx_pad(NF));
+    const int lds = c->lds_max < kLds ? c->lds_max : kLds, cu = c->lds_cu < kLds ? c->lds_cu : kLds;
+    int sets = fx_sets(NF, es, np, lds, cu);
+    const int most = fx_bound(NF, es, np) / fx_group(NF, es, np);
+    if (sets > most) sets = most;
+    const size_t line = (size_t)(NF + (NF >> fx_pad(NF)) + 1) * es;
+    return FxLaunch{sets, dim3(sets > 0 ? (c->d.nz * c->d.nr + sets - 1) / sets : 1),
+                    (size_t)NF * 16 + (size_t)sets * np * line};
   }
   static int theta_sets(const nsc_ctx *c, int adjoint) { return shape(c, adjoint).sets; }
   template <int NI>
