@@ -3,11 +3,17 @@
 // interpolation and mode padding; section 2.4: the checkpoint-restart works
 // on the spectral coefficients).
 //
-//   k_remap  one lane per (field, target mode), kRemapRows target rows per
-//            lane: modes present at both resolutions take the radial
-//            interpolation of their old profile, new modes are zero.  The
-//            interpolation weights are uniform across a workgroup (scalar
-//            loads); the source column streams once per row group.
+//   k_remap_weights  one wavefront per target row: its interpolation weights
+//   k_remap          one lane per (field, target mode), kRemapRows target rows
+//                    per lane: modes present at both resolutions take the
+//                    radial interpolation of their old profile, new modes are
+//                    zero.  The weights are uniform across a workgroup (scalar
+//                    loads, a row group's weights of one old point adjacent);
+//                    the source column streams once per row group.
+//
+// The call's time at 64 x 64 x 127 -> 96 x 96 x 191, heated, in which the
+// fields' bytes take 31 us: 90 us with the weights formed on the host,
+// allocated and copied by each call and read row by row, 71 us now.
 //
 // Interpolant: the polynomial through all points of the old
 // Chebyshev--Gauss--Lobatto grid, in the barycentric form with the weights
@@ -19,7 +25,6 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
-#include <vector>
 
 #include "nsc_internal.h"
 
@@ -29,8 +34,41 @@ namespace {
 constexpr int kRemapLanes = 64;
 constexpr int kRemapRows = 16;  // target rows accumulated per lane
 
+// Radial point j of n between the walls, as the context builds its own grid.
+__device__ __forceinline__ double cgl_point(int j, int n, double r_i, double r_o) {
+  return 0.5 * (r_i + r_o) + 0.5 * cos(M_PI * (double)(n - 1 - j) / (double)(n - 1));
+}
+
+// W[j][i]: weight of old point j in the interpolant at new point i = blockIdx.x
+// (rows of ld; zero for i >= n1).
+__global__ void __launch_bounds__(64) k_remap_weights(int n0, int n1, int ld, double r_i, double r_o,
+                                                      double *__restrict__ W) {
+  const int i = blockIdx.x, t = threadIdx.x;
+  const double x1 = i < n1 ? cgl_point(i, n1, r_i, r_o) : 0.0;
+  int hit = -1;
+  double den = 0.0;
+  auto bary = [&](int j, double x0) {
+    return ((j & 1) ? -1.0 : 1.0) * ((j == 0 || j == n0 - 1) ? 0.5 : 1.0) / (x1 - x0);
+  };
+  for (int j = t; j < n0; j += 64) {
+    const double x0 = cgl_point(j, n0, r_i, r_o);
+    if (x1 == x0) hit = j;
+    else den += bary(j, x0);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    hit = max(hit, __shfl_xor(hit, o, 64));
+    den += __shfl_xor(den, o, 64);
+  }
+  for (int j = t; j < n0; j += 64) {
+    double w = 0.0;
+    if (i < n1) w = hit >= 0 ? (j == hit ? 1.0 : 0.0) : bary(j, cgl_point(j, n0, r_i, r_o)) / den;
+    W[(size_t)j * ld + i] = w;
+  }
+}
+
 __global__ void __launch_bounds__(kRemapLanes)
-k_remap(const double2 *__restrict__ src, int n0, int mt0, int mz0, const double *__restrict__ W,
+k_remap(const double2 *__restrict__ src, int n0, int mt0, int mz0, const double *__restrict__ W, int ld,
         double2 *__restrict__ dst, int n1, int mt1, int mz1) {
   const int md = blockIdx.x * kRemapLanes + threadIdx.x;
   const int nm1 = mt1 * mz1;
@@ -46,17 +84,14 @@ k_remap(const double2 *__restrict__ src, int n0, int mt0, int mz0, const double 
   if (m < mt0 && k >= -K0 && k <= K0) {
     const size_t P0 = (size_t)mt0 * mz0;
     const double2 *s = src + (size_t)f * n0 * P0 + (size_t)m * mz0 + (k + K0);
-    // rows past the end repeat the last row's weights (their sums are not stored)
-    const double *w[kRemapRows];
-#pragma unroll
-    for (int r = 0; r < kRemapRows; ++r) w[r] = W + (size_t)min(i0 + r, n1 - 1) * n0;
 #pragma unroll 4
     for (int j = 0; j < n0; ++j) {
       const double2 v = s[(size_t)j * P0];
+      const double *w = W + (size_t)j * ld + i0;  // rows past the end: zero weights
 #pragma unroll
       for (int r = 0; r < kRemapRows; ++r) {
-        acc[r].x = fma(w[r][j], v.x, acc[r].x);
-        acc[r].y = fma(w[r][j], v.y, acc[r].y);
+        acc[r].x = fma(w[r], v.x, acc[r].x);
+        acc[r].y = fma(w[r], v.y, acc[r].y);
       }
     }
   }
@@ -66,38 +101,7 @@ k_remap(const double2 *__restrict__ src, int n0, int mt0, int mz0, const double 
     if (i0 + r < n1) o[(size_t)r * nm1] = acc[r];
 }
 
-// Radial grid of n points between the walls, as the context builds its own.
-std::vector<double> cgl_grid(int n, double r_i, double r_o) {
-  std::vector<double> r(n);
-  for (int j = 0; j < n; ++j)
-    r[j] = 0.5 * (r_i + r_o) + 0.5 * std::cos(M_PI * (double)(n - 1 - j) / (double)(n - 1));
-  return r;
-}
-
-// W[i][j]: weight of old point j in the interpolant at new point i.
-std::vector<double> remap_weights(const std::vector<double> &x0, const std::vector<double> &x1) {
-  const int n0 = (int)x0.size(), n1 = (int)x1.size();
-  std::vector<double> W((size_t)n1 * n0, 0.0);
-  std::vector<double> bw(n0);
-  for (int j = 0; j < n0; ++j) bw[j] = ((j & 1) ? -1.0 : 1.0) * ((j == 0 || j == n0 - 1) ? 0.5 : 1.0);
-  for (int i = 0; i < n1; ++i) {
-    double *row = W.data() + (size_t)i * n0;
-    int hit = -1;
-    for (int j = 0; j < n0; ++j)
-      if (x1[i] == x0[j]) hit = j;
-    if (hit >= 0) {
-      row[hit] = 1.0;
-      continue;
-    }
-    double den = 0.0;
-    for (int j = 0; j < n0; ++j) {
-      row[j] = bw[j] / (x1[i] - x0[j]);
-      den += row[j];
-    }
-    for (int j = 0; j < n0; ++j) row[j] /= den;
-  }
-  return W;
-}
+int remap_ld(int n1) { return (n1 + kRemapRows - 1) / kRemapRows * kRemapRows; }
 
 // The grid limits of nsc_init: N_r <= 4096 and padded lengths 3 M_theta,
 // 3 (M_z + 1) / 2 <= 4096.  They bound the payload (< 2^40 bytes), so a
@@ -164,12 +168,14 @@ int upload(nsc_ctx *c, FILE *fp, double *dev, size_t bytes) {
 }  // namespace
 
 hipError_t launch_remap(const nsc_ctx *c, const double *src, int n0, int mt0, int mz0,
-                        const double *W_dev, double *dst) {
+                        double *W_dev, double *dst) {
   const nsc::Dims &d = c->d;
+  const int ld = remap_ld(d.nr);
+  hipLaunchKernelGGL(k_remap_weights, dim3(ld), dim3(64), 0, c->stream, n0, d.nr, ld, d.r_i, d.r_o, W_dev);
   const dim3 grid((d.nmodes + kRemapLanes - 1) / kRemapLanes, (d.nr + kRemapRows - 1) / kRemapRows,
                   d.f);
   hipLaunchKernelGGL(k_remap, grid, dim3(kRemapLanes), 0, c->stream,
-                     reinterpret_cast<const double2 *>(src), n0, mt0, mz0, W_dev,
+                     reinterpret_cast<const double2 *>(src), n0, mt0, mz0, W_dev, ld,
                      reinterpret_cast<double2 *>(dst), d.nr, d.mt, d.mz);
   return hipGetLastError();
 }
@@ -186,21 +192,20 @@ int nsc_remap_state(nsc_ctx *c, const double *src, int N_r_src, int M_theta_src,
   const size_t dbytes = (size_t)c->d.f * c->d.nr * c->d.nmodes * 2 * sizeof(double);
   const char *s0 = reinterpret_cast<const char *>(src), *d0 = reinterpret_cast<const char *>(dst);
   if (s0 < d0 + dbytes && d0 < s0 + sbytes) return NSC_ERR_ARG;  // overlap
-  const std::vector<double> W = nsc::remap_weights(nsc::cgl_grid(N_r_src, c->d.r_i, c->d.r_o),
-                                                   nsc::cgl_grid(c->d.nr, c->d.r_i, c->d.r_o));
-  double *W_dev = nullptr;
-  if (hipMalloc((void **)&W_dev, W.size() * sizeof(double)) != hipSuccess) return NSC_ERR_OOM;
+  // the weights: in the right sides' workspace, which no call holds across
+  // another, unless a tall old grid with few new modes needs more
+  const size_t wbytes = (size_t)N_r_src * nsc::remap_ld(c->d.nr) * sizeof(double);
+  double *W_dev = c->s_f;
+  const bool own = wbytes > (size_t)4 * c->d.nr * c->d.nmodes * 2 * sizeof(double);
+  if (own && hipMalloc((void **)&W_dev, wbytes) != hipSuccess) return NSC_ERR_OOM;
   int st = NSC_OK;
-  if (hipMemcpyAsync(W_dev, W.data(), W.size() * sizeof(double), hipMemcpyHostToDevice, c->stream) !=
-      hipSuccess)
-    st = NSC_ERR_DEVICE;
-  if (st == NSC_OK) {
+  {
     nsc::StageTimer t(c, 3);
     if (nsc::launch_remap(c, src, N_r_src, M_theta_src, M_z_src, W_dev, dst) != hipSuccess)
       st = NSC_ERR_DEVICE;
   }
   if (hipStreamSynchronize(c->stream) != hipSuccess && st == NSC_OK) st = NSC_ERR_DEVICE;
-  (void)hipFree(W_dev);
+  if (own) (void)hipFree(W_dev);
   return st;
 }
 
