@@ -151,6 +151,8 @@ constexpr int z_bound(int n) {
 }
 constexpr int z_waves(int n, int esize) { return n > 0 && esize == 8 && z_bound(n) >= 512 ? 4 : 1; }
 
+constexpr int kLds = 160 * 1024;  // gfx950, per compute unit
+
 // Threads per (r, z) line set and LDS pad of the fixed-length theta kernels.
 // One wavefront runs a set without workgroup barriers, but large sets leave
 // too few wavefronts on a compute unit's LDS: above 18 KB of lines (FP64 384
@@ -161,34 +163,55 @@ constexpr int z_waves(int n, int esize) { return n > 0 && esize == 8 && z_bound(
 constexpr int fx_group(int n, int esize, int lines) {
   return n > 768 ? 512 : (n > 512 || lines * lds_line_s<3>(n) * esize > 18 * 1024 ? 256 : 64);
 }
-constexpr int fx_pad(int n) { return n > 768 ? 5 : 3; }
+// Bytes of LDS of `sets` line sets and the twiddles.
+constexpr int fx_lds(int n, int esize, int lines, int pad, int sets) {
+  return n * 16 + sets * lines * (n + (n >> pad) + 1) * esize;
+}
+// Workgroups of that much LDS on a compute unit (allocated in 1280 bytes, with
+// the kernels' static LDS).
+constexpr int fx_per_cu(int shm, int lds_cu) { return lds_cu / ((shm + 512 + 1279) / 1280 * 1280); }
+// Pad period 2^SH of a line.  Shared sets: one slot per 32 where the strides are
+// powers of two (lines of 3 2^a points: reads of consecutive elements then meet no
+// pad in half a wavefront; FP64 768 points 194 -> 162 us, FP32 107 -> 101, heated
+// FP64 384 points 127 -> 120) or where the shorter lines let one more set onto
+// the compute unit (heated FP64 540 points 206 -> 144), else one per 8 (heated
+// FP32 648 points 127 us, 139 with one per 32).
+constexpr int fx_pad(int n, int esize, int lines) {
+  if (n > 768) return 5;
+  if (fx_group(n, esize, lines) == 64) return 3;
+  const int m = n / 3;
+  if ((m & (m - 1)) == 0) return 5;
+  int best = 3;
+  for (int pad = 4; pad <= 5; ++pad)
+    if (fx_per_cu(fx_lds(n, esize, lines, pad, 1), kLds) > fx_per_cu(fx_lds(n, esize, lines, best, 1), kLds))
+      best = pad;
+  return best;
+}
 
-
-// Line sets per workgroup of the fixed-length theta kernels: the number that
-// puts the most sets on a compute unit's LDS (the twiddles are shared), up to
-// 256 threads of one wavefront per set; 0 if one set does not fit.  Where four
-// wavefronts share a set, a larger workgroup has to gain a quarter, as all of
-// it meets at every stage's barriers (FP64 heated 216 points, 8 sets a compute
-// unit in workgroups of four against 7 alone: 158 against 97 us).
+// Line sets per workgroup of the fixed-length theta kernels, 0 if one does not
+// fit: one where several wavefronts share a set, as all of a workgroup meets
+// at every stage's barriers (FP64 heated 216 points, eight sets a compute unit
+// in workgroups of four against seven alone: 158 against 97 us; FP32 600 points
+// 123 against 75, 768 points 126 against 107); of one
+// wavefront per set the number, up to four, that puts the most sets on a
+// compute unit's LDS (they share the twiddles).
 constexpr int fx_sets(int n, int esize, int lines, int lds_max, int lds_cu) {
-  const int G = fx_group(n, esize, lines), pad = fx_pad(n);
-  const int line = (n + (n >> pad) + 1) * esize, tws = n * 16;
+  const int G = fx_group(n, esize, lines), pad = fx_pad(n, esize, lines);
   int best = 0, sets = 0;
-  for (int s = 1; s * G <= (G == 64 ? kThetaWaveThreads : kFftThreads); ++s) {
-    const int shm = tws + s * lines * line;
+  for (int s = 1; s <= (G == 64 ? kThetaWaveThreads / 64 : 1); ++s) {
+    const int shm = fx_lds(n, esize, lines, pad, s);
     if (shm > lds_max) break;
-    const int per_cu = lds_cu / shm * s;
-    if (G == 64 ? per_cu > best : 4 * per_cu >= 5 * best) {
+    const int per_cu = fx_per_cu(shm, lds_cu) * s;
+    if (per_cu > best) {
       best = per_cu;
       sets = s;
     }
   }
   return sets;
 }
-// ... and the launch bound that follows on gfx950's 160 KB: as tight as the
+// ... and the launch bound that follows: as tight as the
 // workgroup, for the registers (a bound of 1024 threads spills in the lines past
 // 480 points)
-constexpr int kLds = 160 * 1024;
 constexpr int fx_bound(int n, int esize, int lines) {
   const int s = fx_sets(n, esize, lines, kLds, kLds);
   return (s < 1 ? 1 : s) * fx_group(n, esize, lines);
@@ -1243,14 +1266,13 @@ struct LenPass {
     int sets = fx_sets(NF, es, np, lds, cu);
     const int most = fx_bound(NF, es, np) / fx_group(NF, es, np);
     if (sets > most) sets = most;
-    const size_t line = (size_t)(NF + (NF >> fx_pad(NF)) + 1) * es;
     return FxLaunch{sets, dim3(sets > 0 ? (c->d.nz * c->d.nr + sets - 1) / sets : 1),
-                    (size_t)NF * 16 + (size_t)sets * np * line};
+                    (size_t)fx_lds(NF, es, np, fx_pad(NF, es, np), sets)};
   }
   static int theta_sets(const nsc_ctx *c, int adjoint) { return shape(c, adjoint).sets; }
   template <int NI>
   static hipError_t theta_run(const nsc_ctx *c, int want_cfl) {
-    constexpr int G = fx_group(NF, sizeof(C2<T>), (NI + 1) / 2), SH = fx_pad(NF);
+    constexpr int G = fx_group(NF, sizeof(C2<T>), (NI + 1) / 2), SH = fx_pad(NF, sizeof(C2<T>), (NI + 1) / 2);
     const FxLaunch L = shape(c, 0);
     if (L.sets == 0) return hipErrorInvalidValue;  // (callers check theta_fits first)
     hipLaunchKernelGGL((k_theta_fx<T, NF, NI, G, SH>), L.grid, dim3(L.sets * G), L.shm, c->stream,
@@ -1264,7 +1286,7 @@ struct LenPass {
   }
   template <int NI>
   static hipError_t theta_adj_run(const nsc_ctx *c) {
-    constexpr int G = fx_group(NF, sizeof(C2<T>), (NI + 1) / 2 + 2), SH = fx_pad(NF);
+    constexpr int G = fx_group(NF, sizeof(C2<T>), (NI + 1) / 2 + 2), SH = fx_pad(NF, sizeof(C2<T>), (NI + 1) / 2 + 2);
     const FxLaunch L = shape(c, 1);
     if (L.sets == 0) return hipErrorInvalidValue;
     hipLaunchKernelGGL((k_theta_adj_fx<T, NF, NI, G, SH>), L.grid, dim3(L.sets * G), L.shm,
