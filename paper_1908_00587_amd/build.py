@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libnsc.so")
 SOURCES = ["nsc_host.cpp", "k_nonlinear.hip", "k_solve.hip", "k_stage.hip", "k_restart.hip",
-           "k_diag.hip", "k_noalloc.hip"] + ["k_len%d.hip" % i for i in range(1, 8)]
+           "k_diag.hip", "k_noalloc.hip"] + ["k_len%d.hip" % i for i in range(1, 13)]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          # packed FP32 instructions are kept out of generated code
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

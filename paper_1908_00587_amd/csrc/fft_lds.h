@@ -587,13 +587,24 @@ __device__ __forceinline__ void ct_stages_ord(LdsC2<T> b0, int nl, LdsTw<T> tw, 
   }
 }
 
+// Lines taken together out of nl: the most a wavefront carries, and where few
+// stages have affine addresses (odd multiples of 1, 2 or 4, an address register
+// per element) no more than about nine values a lane: more spill (three FP32
+// 450-point lines two at a time: 192 us of 18 x 450 sets, 92 one at a time).
+constexpr int ct_group_lines(int n, int nl) {
+  int l = ct_wave_lines(n) < nl ? ct_wave_lines(n) : nl;
+  if (n % 8 != 0)
+    while (l > 1 && l * n > 600) --l;
+  return l;
+}
+
 // Stages S0.. of the order ORD over `nlines` <= NL lines of one wavefront
 // (line stride lds_line<T>(N)), in groups of the lines a wavefront carries.
 template <typename T, bool INV, int N, int ORD, int S0, bool SKIP, int NL>
 __device__ __forceinline__ void fft_wave_ct_ord(C2<T> *buf, int nlines, const TwT<T> *tw,
                                                 int lane) {
-  constexpr int GL = ct_wave_lines(N) < NL ? ct_wave_lines(N) : NL;
-  static_assert(GL > 0, "length too long for a wavefront-scope transform");
+  constexpr int GL = ct_group_lines(N, NL);
+  static_assert(ct_wave_lines(N) > 0, "length too long for a wavefront-scope transform");
   constexpr int LS = lds_line<T>(N);
   LdsTw<T> twl = to_lds_tw<T>(tw);
   for (int l0 = 0; l0 < nlines; l0 += GL) {
