@@ -189,29 +189,29 @@ constexpr int fx_pad(int n, int esize, int lines) {
 }
 
 // Line sets per workgroup of the fixed-length theta kernels, 0 if one does not
-// fit: one where several wavefronts share a set, as all of a workgroup meets
-// at every stage's barriers (FP64 heated 216 points, eight sets a compute unit
-// in workgroups of four against seven alone: 158 against 97 us; FP32 600 points
-// 123 against 75, 768 points 126 against 107); of one
-// wavefront per set the number, up to four, that puts the most sets on a
-// compute unit's LDS (they share the twiddles).
+// fit.  Of one wavefront per set the number, up to four, that puts the most
+// sets on a compute unit's LDS (they share the twiddles).  Where several
+// wavefronts share a set, one, as all of a workgroup meets at every stage's
+// barriers (FP64 heated 216 points, eight sets a compute unit in workgroups of
+// four against seven alone: 158 against 97 us; FP32 600 points 123 against 75,
+// 768 points 126 against 107), unless more double the sets on a compute unit
+// (heated FP32 1536 points, two against one: 2015 against 2307 us of 32 x 1536).
 constexpr int fx_sets(int n, int esize, int lines, int lds_max, int lds_cu) {
   const int G = fx_group(n, esize, lines), pad = fx_pad(n, esize, lines);
   int best = 0, sets = 0;
-  for (int s = 1; s <= (G == 64 ? kThetaWaveThreads / 64 : 1); ++s) {
+  for (int s = 1; s * G <= (G == 64 ? kThetaWaveThreads : kFftThreads); ++s) {
     const int shm = fx_lds(n, esize, lines, pad, s);
     if (shm > lds_max) break;
     const int per_cu = fx_per_cu(shm, lds_cu) * s;
-    if (per_cu > best) {
+    if (G == 64 ? per_cu > best : per_cu >= 2 * best) {
       best = per_cu;
       sets = s;
     }
   }
   return sets;
 }
-// ... and the launch bound that follows: as tight as the
-// workgroup, for the registers (a bound of 1024 threads spills in the lines past
-// 480 points)
+// ... and the launch bound that follows: as tight as the workgroup, for the
+// registers (a bound of 1024 threads spills in the lines past 480 points)
 constexpr int fx_bound(int n, int esize, int lines) {
   const int s = fx_sets(n, esize, lines, kLds, kLds);
   return (s < 1 ? 1 : s) * fx_group(n, esize, lines);
