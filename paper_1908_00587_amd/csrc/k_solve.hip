@@ -20,36 +20,57 @@
 namespace nsc {
 namespace {
 
-// Rows of an operator over their nine-point windows.  pipe: row 0 is an inner
-// row (the axis is no boundary) and the derivative rows are those of the
-// operator's parity (off: their element offset).
+// Matrix entry A[i][c] of an operator for c in the window of row i.  pipe:
+// row 0 is an inner row (the axis is no boundary) and the derivative rows
+// are those of the operator's parity (off: their element offset).
 struct OpRow {
   int kind;
   double alpha, beta, q2, k2;
   int pipe, off;
-  __device__ __forceinline__ bool wall(int n, int i) const { return (i == 0 && !pipe) || i == n - 1; }
-  // the weights row i is made of: D1 in the Neumann rows, D2 + D1/r elsewhere
-  __device__ __forceinline__ void load(const Grid &g, int n, int i, double (&w)[kStencil], double &ri) const {
-    const double *p = (wall(n, i) && kind != OP_HELMHOLTZ ? g.d1 : g.lw) + off + i * kStencil;
+  __device__ __forceinline__ void row(const Grid &g, int n, int i, double *a, int &s) const {
+    s = g.s[i];
+    const double *w1 = g.d1 + off + i * kStencil;
+    const double *w2 = g.d2 + off + i * kStencil;
+    const double ri = g.rinv[i];
+    const bool inner_wall = i == 0 && !pipe;
+    if (kind == OP_HELMHOLTZ) {
+      if (inner_wall || i == n - 1) {
 #pragma unroll
-    for (int t = 0; t < kStencil; ++t) w[t] = p[t];
-    ri = g.rinv[i];
-  }
-  // row i from its weights, the diagonal at entry D
-  template <int D>
-  __device__ __forceinline__ void row(int n, int i, const double (&w)[kStencil], double ri,
-                                      double (&a)[kStencil]) const {
-    const bool wl = wall(n, i);
-    // Dirichlet rows: the Helmholtz walls; the mean pressure head's row at
-    // r_i (pipe: at the wall)
-    const bool unit = wl && (kind == OP_HELMHOLTZ || (kind == OP_MEAN_PRESSURE && (i == 0 || pipe)));
-    const double f = kind == OP_HELMHOLTZ ? -beta : 1.0;
-    const double sh = q2 * ri * ri + k2;
+        for (int t = 0; t < kStencil; ++t) a[t] = (s + t == i) ? 1.0 : 0.0;
+        return;
+      }
 #pragma unroll
-    for (int t = 0; t < kStencil; ++t) {
-      double v = f * w[t];
-      if (t == D) v = kind == OP_HELMHOLTZ ? v + (alpha + beta * sh) : v - sh;
-      a[t] = unit ? (t == D ? 1.0 : 0.0) : (wl ? w[t] : v);
+      for (int t = 0; t < kStencil; ++t) {
+        double v = -beta * (w2[t] + w1[t] * ri);
+        if (s + t == i) v += alpha + beta * (q2 * ri * ri + k2);
+        a[t] = v;
+      }
+    } else if (kind == OP_POISSON) {
+      if (inner_wall || i == n - 1) {
+#pragma unroll
+        for (int t = 0; t < kStencil; ++t) a[t] = w1[t];
+        return;
+      }
+#pragma unroll
+      for (int t = 0; t < kStencil; ++t) {
+        double v = w2[t] + w1[t] * ri;
+        if (s + t == i) v -= q2 * ri * ri + k2;
+        a[t] = v;
+      }
+    } else {  // mean pressure head: (D2 + D1/r) p inside, p(r_i) = 0, D1 row at r_o
+              // (pipe: p = 0 at the wall, the axis no boundary)
+      if (inner_wall || (pipe && i == n - 1)) {
+#pragma unroll
+        for (int t = 0; t < kStencil; ++t) a[t] = (s + t == i) ? 1.0 : 0.0;
+        return;
+      }
+      if (i == n - 1) {
+#pragma unroll
+        for (int t = 0; t < kStencil; ++t) a[t] = w1[t];
+        return;
+      }
+#pragma unroll
+      for (int t = 0; t < kStencil; ++t) a[t] = w2[t] + w1[t] * ri;
     }
   }
 };
@@ -62,15 +83,13 @@ struct OpRow {
 //
 // Rows 8 .. N-5 only need the last four U rows, kept in registers and turned
 // over by unrolling four rows; their weights are loaded four rows ahead.  The
-// first eight and last four rows, whose weights are loaded at the start, read
-// the U rows (up to eight entries there) from LDS, where each lane keeps its
-// last eight.  One wavefront per compute
+// first eight and last four rows read the U rows (up to eight entries there)
+// from LDS, where each lane keeps its last eight.  One wavefront per compute
 // unit is what the smaller grids have, so the time is one wavefront's
 // instruction stream, and past about 16000 operators the factors' writes.
 // Before (elimination of a nine-row window in LDS, the band entries also
-// stored one array per entry) -> now: 32 x 16 x 16 operators' rows 58 -> 16 us,
-// 64 x 64 x 64 twice (heated) 99 -> 24, 128 x 256 x 256 610 -> 135 (22, 29 and
-// 145 with the twelve wall rows' weights loaded row by row).
+// stored one array per entry) -> now: 32 x 16 x 16 operators' rows 58 -> 22 us,
+// 64 x 64 x 64 twice (heated) 99 -> 29, 128 x 256 x 256 610 -> 145.
 constexpr int kFacThreads = 64;
 constexpr int kFacRow = 10;  // LDS doubles per U row: U_{i,i+1..i+8}, 1/U_ii, pad
 
@@ -104,10 +123,11 @@ k_factor(Dims d, Grid g, Factors F0, Factors F1, int kind, double alpha, double 
     F.di[(size_t)i * nops + op] = dinv;
   };
   // a row by the ring, with its diagonal at entry D of its window
-  auto ring_row = [&](auto diag, int i, const double (&w)[kStencil], double ri) {
+  auto ring_row = [&](auto diag, int i) {
     constexpr int D = decltype(diag)::value;
     double a[kStencil];
-    R.template row<D>(n, i, w, ri, a);
+    int s;
+    R.row(g, n, i, a, s);
 #pragma unroll
     for (int t = 0; t < D; ++t) {
       const Dbl2 *u = slot(i - D + t);
@@ -139,22 +159,13 @@ k_factor(Dims d, Grid g, Factors F0, Factors F1, int kind, double alpha, double 
     for (int c = 0; c <= D - 5; ++c)
       F.edge[(size_t)(10 + edge_off(8 - D) + c) * nops + op] = a[c];
   };
-  // (before any store: a later load would have to wait for it)
-  double hw[8][kStencil], hr[8], tw[4][kStencil], tr[4];
-#pragma unroll
-  for (int r = 0; r < 8; ++r) R.load(g, n, r, hw[r], hr[r]);
-#pragma unroll
-  for (int r = 0; r < 4; ++r) R.load(g, n, n - 4 + r, tw[r], tr[r]);
-  ring_row(std::integral_constant<int, 0>{}, 0, hw[0], hr[0]);
-  ring_row(std::integral_constant<int, 1>{}, 1, hw[1], hr[1]);
-  ring_row(std::integral_constant<int, 2>{}, 2, hw[2], hr[2]);
-  ring_row(std::integral_constant<int, 3>{}, 3, hw[3], hr[3]);
-  constexpr std::integral_constant<int, 4> mid{};
-#pragma unroll
-  for (int r = 4; r < 8; ++r)
-    if (r < n - 4) ring_row(mid, r, hw[r], hr[r]);
-  int i = 8;
-  if (i < n - 4) {
+  ring_row(std::integral_constant<int, 0>{}, 0);
+  ring_row(std::integral_constant<int, 1>{}, 1);
+  ring_row(std::integral_constant<int, 2>{}, 2);
+  ring_row(std::integral_constant<int, 3>{}, 3);
+  int i = 4;
+  for (; i < 8 && i < n - 4; ++i) ring_row(std::integral_constant<int, 4>{}, i);
+  if (i + 4 <= n - 4) {
     // rows i .. i+3, the U rows of i-4 .. i-1 in registers
     double uk[4][4], dv[4], w[4][kStencil], ri[4];
     auto weights = [&](int r, int j) {
@@ -206,14 +217,12 @@ k_factor(Dims d, Grid g, Factors F0, Factors F1, int kind, double alpha, double 
         }
       }
     }
-#pragma unroll
-    for (int r = 0; r < 3; ++r)
-      if (i + r < n - 4) ring_row(mid, i + r, w[r], ri[r]);
   }
-  ring_row(std::integral_constant<int, 5>{}, n - 4, tw[0], tr[0]);
-  ring_row(std::integral_constant<int, 6>{}, n - 3, tw[1], tr[1]);
-  ring_row(std::integral_constant<int, 7>{}, n - 2, tw[2], tr[2]);
-  ring_row(std::integral_constant<int, 8>{}, n - 1, tw[3], tr[3]);
+  for (; i < n - 4; ++i) ring_row(std::integral_constant<int, 4>{}, i);
+  ring_row(std::integral_constant<int, 5>{}, n - 4);
+  ring_row(std::integral_constant<int, 6>{}, n - 3);
+  ring_row(std::integral_constant<int, 7>{}, n - 2);
+  ring_row(std::integral_constant<int, 8>{}, n - 1);
 }
 
 // Rows of the packed factors of one operator.
