@@ -33,6 +33,7 @@ namespace {
 
 constexpr int kRemapLanes = 64;
 constexpr int kRemapRows = 16;  // target rows accumulated per lane
+constexpr size_t kRemapKeep = (size_t)8 << 20;  // bytes of weights a context keeps (1024 x 1024 points)
 
 // Radial point j of n between the walls, as the context builds its own grid.
 __device__ __forceinline__ double cgl_point(int j, int n, double r_i, double r_o) {
@@ -192,12 +193,21 @@ int nsc_remap_state(nsc_ctx *c, const double *src, int N_r_src, int M_theta_src,
   const size_t dbytes = (size_t)c->d.f * c->d.nr * c->d.nmodes * 2 * sizeof(double);
   const char *s0 = reinterpret_cast<const char *>(src), *d0 = reinterpret_cast<const char *>(dst);
   if (s0 < d0 + dbytes && d0 < s0 + sbytes) return NSC_ERR_ARG;  // overlap
-  // the weights: in the right sides' workspace, which no call holds across
-  // another, unless a tall old grid with few new modes needs more
+  // the weights have memory of their own: the workspaces belong to the calls
+  // that may still be running on another stream.  Kept for the next restart
+  // (this call waits for its stream, so nothing reads them any more) unless
+  // large
   const size_t wbytes = (size_t)N_r_src * nsc::remap_ld(c->d.nr) * sizeof(double);
-  double *W_dev = c->s_f;
-  const bool own = wbytes > (size_t)4 * c->d.nr * c->d.nmodes * 2 * sizeof(double);
-  if (own && hipMalloc((void **)&W_dev, wbytes) != hipSuccess) return NSC_ERR_OOM;
+  const bool keep = wbytes <= nsc::kRemapKeep;
+  double *W_dev = c->remap_w;
+  if (!keep || wbytes > c->remap_wbytes) {
+    if (hipMalloc((void **)&W_dev, wbytes) != hipSuccess) return NSC_ERR_OOM;
+    if (keep) {
+      if (c->remap_w) (void)hipFree(c->remap_w);
+      c->remap_w = W_dev;
+      c->remap_wbytes = wbytes;
+    }
+  }
   int st = NSC_OK;
   {
     nsc::StageTimer t(c, 3);
@@ -205,7 +215,7 @@ int nsc_remap_state(nsc_ctx *c, const double *src, int N_r_src, int M_theta_src,
       st = NSC_ERR_DEVICE;
   }
   if (hipStreamSynchronize(c->stream) != hipSuccess && st == NSC_OK) st = NSC_ERR_DEVICE;
-  if (own) (void)hipFree(W_dev);
+  if (!keep) (void)hipFree(W_dev);
   return st;
 }
 

@@ -338,7 +338,7 @@ int nsc_destroy(nsc_ctx *c) {
   void *ptrs[] = {c->tables, c->tw64_t, c->tw64_z, c->tw32_t, c->tw32_z, c->zbuf, c->wbuf,
                   c->cfl_part, c->cfl_val, c->e_part, c->s_f, c->s_g, c->s_p, c->s_x,
                   c->s_lam, c->s_vjp, c->s_u1, c->s_nn, c->s_nq, c->s_adj, c->s_mean, c->inf.resp, c->inf.ainv,
-                  c->t_row, c->t_cnt, c->t_wt, c->t_wd};
+                  c->t_row, c->t_cnt, c->t_wt, c->t_wd, c->remap_w};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
   free_factors(&c->fv);

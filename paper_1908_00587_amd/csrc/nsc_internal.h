@@ -134,6 +134,8 @@ struct nsc_ctx {
   double *s_nq = nullptr;   // [F][N_r][modes] complex N^q
   double *s_tmp = nullptr;  // [F][N_r][modes] initial-state scratch (shares s_u1's memory)
   double *s_adj = nullptr;  // [n_in][N_r][modes] complex adjoint of the derived fields
+  double *remap_w = nullptr;  // restart weights (nsc_remap_state alone), remap_wbytes of them
+  size_t remap_wbytes = 0;
   double *s_mean = nullptr;  // [8][N_r] mean-flow profiles of the current nonlinear call
   double *h_pinned = nullptr;  // pinned host scalar(s)
   double *h_pinned_dev = nullptr;  // its device-side address (kernels write the CFL bound)
