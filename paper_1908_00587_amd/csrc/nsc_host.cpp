@@ -512,8 +512,9 @@ static int init_impl(nsc_ctx *c, double eta, double Re_i, double Re_o, double Ra
   HIPCHK(hipMemcpy(p_s, s.data(), n * sizeof(int), hipMemcpyHostToDevice));
   c->g = Grid{p_r, p_rinv, p_d1, p_d2, p_s, p_dr, p_cc, p_lw, pipe ? nw : 0};
   // the adjoint's transposed rows of D2 + D1/r and of D1: column j collects the rows
-  // whose windows hold it (nine inside, up to thirteen where the one-sided
-  // wall windows overlap)
+  // whose windows hold it (nine inside, up to thirteen next to the one-sided
+  // wall windows, every row in the middle columns of up to 17 points, where
+  // the two walls' windows overlap: at 17 points column 8 lies in all 17)
   {
     std::vector<int> trow((size_t)n * kTrans, 0), tcnt(n, 0);
     std::vector<double> twt((size_t)n * kTrans, 0.0), twd((size_t)n * kTrans, 0.0);

@@ -12,7 +12,7 @@ namespace nsc {
 
 constexpr int kStencil = 9;    // nine-point radial stencils (section 2.1 default)
 constexpr int kHalf = 4;       // stencil half width
-constexpr int kTrans = 16;     // slots per column of a transposed stencil (13 used at most)
+constexpr int kTrans = 2 * kStencil - 1;  // slots per column of a transposed stencil (13 used from 18 points on)
 constexpr int kEdge = 20;      // extra U entries of rows 0..3 + extra L of rows N-4..N-1
 constexpr int kMaxRadix = 8;
 constexpr int kMaxStages = 12;
