@@ -210,12 +210,28 @@ int nonlinear_impl(nsc_ctx *c, const double *u, double *nh, double *cfl_out,
   return NSC_OK;
 }
 
+// Whether the pressure lies over the input state `in` such that a mode's entries
+// of the one are another mode's of the other.  A workgroup of the one-kernel
+// stage has read all of its modes' columns before it writes them, and no
+// other's, so an overlap by whole planes is harmless.
+bool crosses_modes(const Dims &d, const double *in, const double *p) {
+  const size_t plane = (size_t)d.nmodes * 16;
+  const char *a = reinterpret_cast<const char *>(in), *b = reinterpret_cast<const char *>(p);
+  if (!(b < a + plane * d.nr * d.f && a < b + plane * d.nr)) return false;
+  return (size_t)(a < b ? b - a : a - b) % plane != 0;
+}
+
 int solve_impl(nsc_ctx *c, const double *un, const double *nn, const double *nq, double *out,
                double *pout, double dt, double cc, int walls) {
   TRY(ensure_factors(c, dt, cc));
   if (c->fused) {
     StageTimer t(c, 9);
-    HIPCHK(launch_stage(c, un, nn, nq, out, pout, dt, cc, walls));
+    const Dims &d = c->d;
+    const bool by_way =
+        pout && (crosses_modes(d, un, pout) || (nn && (crosses_modes(d, nn, pout) || crosses_modes(d, nq, pout))));
+    HIPCHK(launch_stage(c, un, nn, nq, out, by_way ? c->s_p : pout, dt, cc, walls));
+    if (by_way)
+      HIPCHK(hipMemcpyAsync(pout, c->s_p, (size_t)d.nr * d.nmodes * 16, hipMemcpyDeviceToDevice, c->stream));
     return NSC_OK;
   }
   {
