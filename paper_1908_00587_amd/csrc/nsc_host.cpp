@@ -586,11 +586,15 @@ static int init_impl(nsc_ctx *c, double eta, double Re_i, double Re_o, double Ra
   TRY(dmalloc((void **)&c->cfl_val, 4 * sizeof(double)));
   c->e_nblk = 1024;
   TRY(dmalloc((void **)&c->e_part, (size_t)c->e_nblk * sizeof(double)));
-  TRY(dmalloc((void **)&c->s_f, field * 4));
-  TRY(dmalloc((void **)&c->s_g, field));
+  c->fused = stage_fused(c) ? 1 : 0;
+  c->fused_adj = stage_adj_fused(c) ? 1 : 0;
   TRY(dmalloc((void **)&c->s_p, field));
-  TRY(dmalloc((void **)&c->s_x, field * 4));
-  TRY(dmalloc((void **)&c->s_lam, (size_t)d.nmodes * 32));
+  if (!c->fused || (!pipe && !c->fused_adj)) {  // (the pipe has no adjoint)
+    TRY(dmalloc((void **)&c->s_f, field * 4));
+    TRY(dmalloc((void **)&c->s_g, field));
+    TRY(dmalloc((void **)&c->s_x, field * 4));
+    TRY(dmalloc((void **)&c->s_lam, (size_t)d.nmodes * 32));
+  }
   TRY(dmalloc((void **)&c->s_u1, field * d.f));
   TRY(dmalloc((void **)&c->s_nn, field * d.f));
   TRY(dmalloc((void **)&c->s_nq, field * d.f));
@@ -605,8 +609,6 @@ static int init_impl(nsc_ctx *c, double eta, double Re_i, double Re_o, double Ra
 
   // factors
   const int kp1 = d.kmax + 1;
-  c->fused = stage_fused(c) ? 1 : 0;
-  c->fused_adj = stage_adj_fused(c) ? 1 : 0;
   TRY(alloc_factors(&c->fv, d.mt + 1, kp1, n));
   TRY(alloc_factors(&c->fp, d.mt, kp1, n));
   if (d.heated) TRY(alloc_factors(&c->ft, d.mt, kp1, n));

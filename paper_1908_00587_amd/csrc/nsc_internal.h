@@ -119,9 +119,11 @@ struct nsc_ctx {
   double *cfl_val = nullptr;   // [2] scalars
   double *e_part = nullptr;    // energy partials
   int e_nblk = 0;
+  // (s_f, s_g, s_x, s_lam: only where the stage or its adjoint runs as the
+  // kernel sequence)
   double *s_f = nullptr;    // [4][N_r][modes] complex right sides
   double *s_g = nullptr;    // [N_r][modes] complex divergence
-  double *s_p = nullptr;    // [N_r][modes] complex p0
+  double *s_p = nullptr;    // [N_r][modes] complex p0; pressure on its way to an array over an input
   double *s_x = nullptr;    // [4][N_r][modes] complex X0+, X0-, X0z, T
   double *s_lam = nullptr;  // [modes][2] complex
   // transposed rows of D2 + D1/r (cylinders): column j's entries (row,
