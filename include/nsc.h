@@ -146,7 +146,8 @@ int nsc_nonlinear(nsc_ctx *ctx, const double *u_hat, double *n_hat,
  *   pressure Poisson with Neumann rows, Helmholtz solves (I/dt - c L) X,
  *   influence-matrix correction making div u = 0 at both walls,
  * using the step set by nsc_set_timestep.  u_hat_n, n_hat_n, n_hat_q,
- * u_hat_out: [F][N_r][M_theta][M_z]; u_hat_out must not alias the inputs.
+ * u_hat_out: [F][N_r][M_theta][M_z]; u_hat_out must not alias the inputs
+ * (p_hat_out may overlap them, not u_hat_out).
  * p_hat_out: NULL or [N_r][M_theta][M_z] pressure head (mode (0,0): the
  * solution of dp/dr = F_r = c N^q_r + (1-c) N^n_r in divergence form,
  * (D2 + D1/r) p = (D1 + 1/r) F_r, with p(r_i) = 0 and D1 p = F_r at r_o). */

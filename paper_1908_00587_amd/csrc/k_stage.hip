@@ -10,6 +10,9 @@
 //   right sides f -> divergence -> pressure (and temperature) sweeps ->
 //   velocity right sides -> velocity sweeps -> influence coefficients ->
 //   superposition, +- -> (r, theta).
+// The new state may replace u^n (nsc_step does): no other workgroup touches
+// these columns, and every read of u^n, N^n, N^q lies before the barrier ahead
+// of the pressure sweeps, every store behind it.
 // The stencil phases run over (row, mode) items, RPT consecutive rows per
 // thread, from columns in LDS; the sweeps run on one lane per real column,
 // four lanes ((+-k) x (Re, Im)) per operator, with the factor rows staged
@@ -1221,10 +1224,21 @@ StageShape shape_for(const nsc_ctx *c, bool adjoint) {
 }
 
 // Eight |k| per workgroup (whole 128-byte lines of sixteen modes, half the
-// workgroups) once that leaves a workgroup per compute unit, as long as two
-// such workgroups fit one; four otherwise, also for the adjoint at 17 and 18
-// points, where a pair of rows has every row of the column in its transposed
-// windows.
+// workgroups) once that leaves a workgroup per compute unit; four otherwise,
+// past 64 points, where a thread would hold more than four rows, and for the
+// adjoint at 17 and 18 points, where a pair of rows has every row of the column
+// in its transposed windows.  us with four / eight |k|, isothermal:
+//                        stage          adjoint
+//   48 x 40 x 79  (200 tiles of eight)  22.8 / 23.0    33.4 / 35.7
+//   48 x 45 x 89  (270)                 37.8 / 30.4    54.8 / 44.1
+//   48 x 64 x 127 (512)                 43.9 / 34.0    63.8 / 48.1
+//   64 x 40 x 79  (200)                 27.5 / 32.1    38.9 / 56.6
+//   64 x 64 x 127 (512)                 53.6 / 46.2    76.2 / 78.8
+// On 32 points the two meet at the line (16.4 / 16.3 at 200 tiles, 20.0 / 21.1
+// at 270), on 16 a little below it.  From 49 points on, four rows per thread
+// spill with the temperature (79 registers; 11 without) and in the adjoint (92 and
+// 56): there the line is not the best one (64 x 64 x 127 heated 60.3 / 71.0,
+// adjoint 86.1 / 110.7).
 StageShape stage_shape(const nsc_ctx *c, bool adjoint) {
   const int n = c->d.nr;
   const long tiles = (long)c->d.mt * ((c->d.kmax + 8) / 8);

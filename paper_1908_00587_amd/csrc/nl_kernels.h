@@ -28,8 +28,8 @@ namespace nsc {
 // instantiates its own lengths)
 namespace {
 
-constexpr int kMaxB = 1;
-constexpr int kThetaWaveThreads = 256;  // at most four line sets per workgroup  // one butterfly per thread per stage: low register use, high occupancy
+constexpr int kMaxB = 1;  // one butterfly per thread per stage: low register use, high occupancy
+constexpr int kThetaWaveThreads = 256;  // at most four line sets per workgroup
 
 // Items (row, col) of a rows x cols index space taken by thread t of n in
 // row-major order (item t + i n), stepped without a division per item.

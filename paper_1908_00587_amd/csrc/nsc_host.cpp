@@ -709,8 +709,10 @@ int nsc_step(nsc_ctx *c, double *u, double *dt_inout) {
   // scalar; the event marks it
   TRY(nonlinear_impl(c, u, c->s_nn, c->cfl_val, c->h_pinned_dev));
   HIPCHK(hipEventRecord(c->ev_cfl, c->stream));
-  // predictor, then correctors; the last stage writes u in place (the
-  // finalising kernel reads only library scratch, never u^n)
+  // predictor, then correctors; the last stage writes u in place.  In the
+  // kernel sequence the finalising kernel reads only library scratch, never
+  // u^n; the one-kernel stage reads all rows of a mode's columns before it
+  // writes the first, and one workgroup alone reads and writes them
   TRY(solve_impl(c, u, c->s_nn, c->s_nn, c->n_corr == 0 ? u : c->s_u1, nullptr, dt, c->c, 1));
   for (int q = 1; q <= c->n_corr; ++q) {
     TRY(nonlinear_impl(c, c->s_u1, c->s_nq, nullptr));
