@@ -233,7 +233,7 @@ int nsc_step_vjp(nsc_ctx *ctx, const double *u_hat, const double *stages,
  * (F * N_r * M_theta * M_z * 16 bytes) -- larger ones return NSC_ERR_ARG
  * before any device work.  Every context on a device shares that array, so
  * calls that overlap on one device (any contexts, any streams) race; the
- * array keeps the last call's contents and each call clears what it needs.
+ * array keeps the last call's contents; a call writes all that it reads.
  * Same arguments and other errors as nsc_step_vjp; NSC_ERR_DEVICE if the
  * array's address could not be obtained when the context was created. */
 int nsc_step_vjp_noalloc(nsc_ctx *ctx, const double *u_hat, const double *stages,

@@ -89,7 +89,7 @@ struct OpRow {
 // instruction stream, and past about 16000 operators the factors' writes.
 // Before (elimination of a nine-row window in LDS, the band entries also
 // stored one array per entry) -> now: 32 x 16 x 16 operators' rows 58 -> 22 us,
-// 64 x 64 x 64 twice (heated) 99 -> 29, 128 x 256 x 256 610 -> 145.
+// 64 x 64 x 64 twice (heated) 99 -> 30, 128 x 256 x 256 610 -> 145 to 175.
 constexpr int kFacThreads = 64;
 constexpr int kFacRow = 10;  // LDS doubles per U row: U_{i,i+1..i+8}, 1/U_ii, pad
 
@@ -447,8 +447,8 @@ __device__ __forceinline__ void influence_matrix(const Dims &d, const Grid &g, c
 // operator, the factor rows loaded eight ahead; all threads write the columns out.
 // What bounds it is the serial sweep of a lane.
 // Before (one lane per operator and kind with its own LDS columns, the matrices
-// in a second kernel) -> now: 32 x 16 x 16 31 -> 16 us, 64 x 64 x 64 51 -> 22;
-// 128 x 256 x 256 720 -> 730 (one workgroup per compute unit). With eight
+// in a second kernel) -> now: 32 x 16 x 16 31 -> 15 us, 64 x 64 x 64 51 -> 22;
+// 128 x 256 x 256 720 -> 670 (one workgroup per compute unit). With eight
 // operators per workgroup: 15, 34 and 839 us.
 constexpr int kInfOps = 16;
 constexpr int kInfThreads = 256;

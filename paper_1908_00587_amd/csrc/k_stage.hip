@@ -23,15 +23,16 @@
 // divergence, p0, X0, each through HBM or the last-level cache) and read each
 // factor row twice, once per sign of k; this reads 2.5 to 3.5 states and the
 // factors and writes one state.  Measured per stage, sequence -> this:
-// 32 points x 16 x 31 modes 34 -> 14 us, heated 64 x 64 x 127 109 -> 70 us,
-// pipe 64 x 64 x 127 97 -> 47 us, 128 x 256 x 511 2840 -> 1740 us (6.6 GB of
-// counted traffic, 3.8 TB/s).  What bounds it: on the large grid the fetched
+// 32 points x 16 x 31 modes 34 -> 14 us, heated 64 x 64 x 127 109 -> 73 us,
+// pipe 64 x 64 x 127 97 -> 47 us, 128 x 256 x 511 2840 -> 1840 us (6.4 GB of
+// counted traffic, 3.5 TB/s).  What bounds it: on the large grid the fetched
 // bytes and, with two workgroups' columns filling a compute unit's LDS, the
 // latency of the recurrences (two workgroups of eight modes take turns in
 // loading and sweeping); on the small ones the latency alone.  The registers
 // of the phases are kept below 256 by hand (loads issued one phase ahead, not
 // two; scheduling barriers), because spills cost more than the latency they
-// hide: 65 spilled registers wrote 1.1 GB per launch on 128 x 256 x 511.
+// hide: 65 spilled registers wrote 1.1 GB per launch on 128 x 256 x 511.  Four
+// rows per thread still spill 11, with the temperature 79.
 #include <cfloat>
 #include <type_traits>
 
