@@ -88,14 +88,15 @@ def kernel_bytes(name, w, prec):
 
 # device kernels behind each timed stage in mixed precision, by name prefix
 # (template arguments depend on the grid and geometry: transform lengths,
-# field counts, line-set shapes, the LDS or global-memory sweep)
+# field counts, line-set shapes); the parts of the implicit stage run in one
+# kernel up to 128 radial points, as a sequence past that
+STAGE = "nsc::k_stage<"
 STAGE_KERNELS = {"theta": ("nsc::k_theta<float,", "nsc::k_theta_fx<float,"),
                  "zinv": ("nsc::k_zinv<float,",), "zfwd": ("nsc::k_zfwd<float,",),
-                 "rhs": ("nsc::k_rhs<",), "div": ("nsc::k_div2<",),
-                 "sweep_pt": ("nsc::k_sweep<true, 0,", "nsc::k_sweep<false, 0,", "nsc::k_sweep<0>"),
-                 "sweep_vel": ("nsc::k_sweep<true, 1,", "nsc::k_sweep<false, 1,", "nsc::k_sweep<1>"),
-                 "vel_rhs": ("nsc::k_vel_rhs<",), "finalize": ("nsc::k_finalize<false>",),
-                 "influence": ("nsc::k_influence<",), "stage": ("nsc::k_stage<",)}
+                 "rhs": ("nsc::k_rhs<", STAGE), "div": ("nsc::k_div2<", STAGE),
+                 "sweep_pt": ("nsc::k_sweep<0>", STAGE), "sweep_vel": ("nsc::k_sweep<1>", STAGE),
+                 "vel_rhs": ("nsc::k_vel_rhs<", STAGE), "finalize": ("nsc::k_finalize<false>", STAGE),
+                 "influence": ("nsc::k_influence<", STAGE), "stage": (STAGE,)}
 
 
 def source_digest():
